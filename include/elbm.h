@@ -75,10 +75,12 @@ extern "C" {
 #define ELBM_FLAG_SCALAR_KERNEL 1 /* always use the one-node-per-thread step kernel. By
                                      default rows of nx = 64 V W nodes (W <= 8) use the
                                      row-vector kernel (V nodes per lane), other rows the
-                                     one-node-per-thread kernel; results of the two are
-                                     bitwise equal. */
+                                     one-node-per-thread kernel; elbm_step and
+                                     elbm_step_record may take two steps per launch where
+                                     that is faster; results are bitwise equal. */
 #define ELBM_VECTOR_WIDTH_SHIFT 4 /* (flags >> 4) & 0xF: nodes per lane V in {1, 2, 4} of
-                                     the row-vector kernel; 0 = automatic */
+                                     the row-vector kernel (then one step per launch);
+                                     0 = automatic */
 #define ELBM_FLAG_REST_FP32 2     /* BF16 / FP16 only: the rest population is stored in FP32
                                      and takes up the rounding residuals of the 18 moving
                                      populations of its node, so the stored mass equals

@@ -18,8 +18,11 @@ CSRC = os.path.join(HERE, "csrc")
 BUILD = os.path.join(HERE, "_build")
 LIBS = {19: os.path.join(HERE, "libelbm.so"), 27: os.path.join(HERE, "libelbm27.so")}
 LIB = LIBS[19]
-SOURCES = ["step_f64.hip", "step_f32.hip", "step_bf16.hip", "step_fp16.hip", "step.hip", "aux.hip",
-           "api.hip"]
+SOURCES = ["step_f64.hip", "step_f32.hip", "step_bf16.hip", "step_fp16.hip", "pair_f64.hip",
+           "pair_f32.hip", "step.hip", "aux.hip", "api.hip"]
+# flags of single units: the two-step kernels keep no FP64 literals in registers across their
+# sweep (hoisted out of its loop they cost 10-60 VGPRs and spilled)
+UNIT_FLAGS = {src: ["-mllvm", "-disable-machine-licm"] for src in ("pair_f64.hip", "pair_f32.hip")}
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 
 FLAGS = [
@@ -35,7 +38,7 @@ FLAGS = [
 
 def _compile(src: str, q: int, verbose: bool) -> str:
     obj = os.path.join(BUILD, f"q{q}", os.path.splitext(src)[0] + ".o")
-    cmd = [HIPCC, *FLAGS, f"-DELBM_Q={q}", "-c", os.path.join(CSRC, src), "-o", obj]
+    cmd = [HIPCC, *FLAGS, *UNIT_FLAGS.get(src, []), f"-DELBM_Q={q}", "-c", os.path.join(CSRC, src), "-o", obj]
     if verbose:
         print(" ".join(cmd), flush=True)
     subprocess.run(cmd, check=True)

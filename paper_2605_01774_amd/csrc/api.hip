@@ -274,6 +274,11 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
         delete h;
         return hip_fail(e, "hipGetDevice");
     }
+    e = hipDeviceGetAttribute(&h->cus, hipDeviceAttributeMultiprocessorCount, h->device);
+    if (e != hipSuccess) {
+        delete h;
+        return hip_fail(e, "hipDeviceGetAttribute");
+    }
     if (int r = resolve_scratch(h->device)) {
         delete h;
         return r;
@@ -511,6 +516,25 @@ static int advance(elbm_lattice* h, const void* src, void* dst, void* lam_rec, u
     return ELBM_OK;
 }
 
+// Two time steps in one launch, as two advance() calls; *done false where the two-step kernel
+// does not take the lattice (nothing is launched then).
+static int advance_pair(elbm_lattice* h, const void* src, void* dst, void* const (&lam)[2], uint8_t* const (&br)[2],
+                        bool* done) {
+    StepPair p;
+    p.mult[0] = (h->pending ? 0.5 * h->pending_scale : 0.0) + 0.5 * h->src_scale;
+    p.mult[1] = (h->r_mode != 0 ? 0.5 * h->src_scale : 0.0) + 0.5 * h->src_scale;
+    for (int m = 0; m < 2; ++m) {
+        p.lam[m] = lam[m];
+        p.br[m] = br[m];
+    }
+    HIP_OK(launch_step_pair(h, src, dst, p, done), "step pair");
+    if (!*done) return ELBM_OK;
+    h->pending = h->r_mode != 0;
+    h->pending_scale = h->src_scale;
+    h->time += 2;
+    return ELBM_OK;
+}
+
 static int do_steps(elbm_lattice* h, int64_t n_steps, void* lam_rec, uint8_t* br_rec) {
     if (int r = check_handle(h)) return r;
     if (int r = check_bound(h)) return r;
@@ -519,7 +543,22 @@ static int do_steps(elbm_lattice* h, int64_t n_steps, void* lam_rec, uint8_t* br
     if (!h->t_set) return fail(ELBM_ESTATE, "diffusion tensor not set");
     if (int r = set_device(h)) return r;
     const int rb = real_bytes(h->cfg.precision);
+    bool pairs = true;
     for (int64_t s = 0; s < n_steps; ++s) {
+        if (pairs && s + 2 <= n_steps) {
+            void* lam[2];
+            uint8_t* br[2];
+            for (int m = 0; m < 2; ++m) {
+                lam[m] = lam_rec ? static_cast<char*>(lam_rec) + (s + m) * h->n * rb : nullptr;
+                br[m] = br_rec ? br_rec + (s + m) * h->n : nullptr;
+            }
+            if (int r = advance_pair(h, h->buf[h->cur], h->buf[h->cur ^ 1], lam, br, &pairs)) return r;
+            if (pairs) {
+                h->cur ^= 1;
+                s += 1;
+                continue;
+            }
+        }
         void* lr = lam_rec ? static_cast<char*>(lam_rec) + s * h->n * rb : nullptr;
         uint8_t* br = br_rec ? br_rec + s * h->n : nullptr;
         if (int r = advance(h, h->buf[h->cur], h->buf[h->cur ^ 1], lr, br)) return r;

@@ -158,6 +158,9 @@ __device__ __forceinline__ void node_coef(const StepArgs<Real>& a, int k, NodeCo
     }
 }
 
+// Hash of a time step, mixed into the seeds of the stochastic rounding.
+inline uint32_t step_mix(int64_t time) { return pcg_hash(uint32_t(time) ^ 0x9E3779B9u); }
+
 template <class Real>
 inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
     StepArgs<Real> a{};
@@ -195,7 +198,7 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
     a.src_mult = Real(src_mult);
     a.rest32 = (h->cfg.flags & ELBM_FLAG_REST_FP32) ? 1 : 0;
     a.sround = (h->cfg.flags & ELBM_FLAG_STOCHASTIC_ROUNDING) ? 1 : 0;
-    a.tmix = pcg_hash(uint32_t(h->time) ^ 0x9E3779B9u);
+    a.tmix = step_mix(h->time);
     a.xcd_remap = 0;
     a.phi_lo = Real(h->phi_lo);
     a.phi_hi = Real(h->phi_hi);

@@ -10,6 +10,7 @@ struct elbm_lattice {
     elbm_config cfg;
     int64_t n = 0;            // nodes
     int device = 0;
+    int cus = 0;              // compute units of the device
     hipStream_t stream = nullptr;
     void* buf[2] = {nullptr, nullptr};
     int cur = 0;              // buffer holding the current state
@@ -60,6 +61,14 @@ inline int real_bytes(int precision) { return precision == ELBM_F64 ? 8 : 4; }
 // All launchers enqueue on h->stream and return the launch status.
 hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double src_mult,
                        void* lam_rec, uint8_t* br_rec);
+// Two steps from src to dst in one launch, where the tiled kernel takes the lattice (*done
+// tells): their source multipliers and records (null: none).
+struct StepPair {
+    double mult[2];
+    void* lam[2];
+    uint8_t* br[2];
+};
+hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done);
 hipError_t launch_adjoint(const elbm_lattice* h, const void* state, double src_mult,
                           const void* lam_rec, const uint8_t* br_rec, const void* adj_in,
                           void* adj_out, void* t_grad);

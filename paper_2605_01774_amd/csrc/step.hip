@@ -14,6 +14,8 @@ ELBM_FORM_DECL(f32)
 ELBM_FORM_DECL(bf16)
 ELBM_FORM_DECL(fp16)
 #undef ELBM_FORM_DECL
+hipError_t launch_step_pair_f64(const elbm_lattice*, const void*, void*, const StepPair&, bool*);
+hipError_t launch_step_pair_f32(const elbm_lattice*, const void*, void*, const StepPair&, bool*);
 
 hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double src_mult,
                        void* lam_rec, uint8_t* br_rec) {
@@ -22,6 +24,15 @@ hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double
         case ELBM_F32: return launch_step_f32(h, src, dst, src_mult, lam_rec, br_rec);
         case ELBM_BF16: return launch_step_bf16(h, src, dst, src_mult, lam_rec, br_rec);
         default: return launch_step_fp16(h, src, dst, src_mult, lam_rec, br_rec);
+    }
+}
+
+hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done) {
+    *done = false;
+    switch (h->cfg.precision) {
+        case ELBM_F64: return launch_step_pair_f64(h, src, dst, p, done);
+        case ELBM_F32: return launch_step_pair_f32(h, src, dst, p, done);
+        default: return hipSuccess;
     }
 }
 
