@@ -116,7 +116,10 @@ __global__ __launch_bounds__(NT, sizeof(Real) == 4 ? 4 : 2) void k_step_pair(con
                                                                              const PairArgs<Real> g) {
     constexpr int SB = int(sizeof(Real));
     constexpr bool CM = sizeof(Real) == 4;  // compensated mass sum (FP32 storage)
-    __shared__ Real lds[pair_slots<ABB>()][NT];
+    // one value more at each end: the columns beside a Dirichlet plane at a row's end are read
+    // before the wall node's own value replaces them
+    __shared__ Real lds_all[pair_slots<ABB>() * NT + 2];
+    Real(*const lds)[NT] = reinterpret_cast<Real(*)[NT]>(lds_all + 1);
 
     // Blocks go to the eight XCDs in turn: each XCD takes a contiguous eighth of the tiles, so
     // that neighbours share the halo's lines in its L2.
@@ -143,8 +146,8 @@ __global__ __launch_bounds__(NT, sizeof(Real) == 4 ? 4 : 2) void k_step_pair(con
     // the column whose neighbours this thread reads, and where they are in x
     const int tc = inner ? t : cw + hx;
     const int lc = inner ? lx : hx;
-    const int xl = !ABB && lc == 0 ? cw - 1 : -1, xr = !ABB && lc == cw - 1 ? 1 - cw : 1;
     const bool lo = ABB && gx == 0, hi = ABB && gx == nx - 1;
+    const int xl = !ABB && lc == 0 ? cw - 1 : -1, xr = !ABB && lc == cw - 1 ? 1 - cw : 1;
 
     // Every access is a scalar base (plane and run) plus one of the thread's byte offsets
     // within a plane, which pair_plan keeps below 2^31.
