@@ -117,16 +117,15 @@ constexpr bool storage_units() {
     return std::is_same<ST, _Float16>::value && !ROOT;
 }
 
-template <class ST, int UM, bool ROOT, bool ABB, bool RS>
+template <class ST, int UM, bool ROOT, bool ABB, bool RS, bool ROW>
 __global__ __launch_bounds__(512) void k_step(const StepArgs<typename Store<ST>::Real> a) {
     using Real = typename Store<ST>::Real;
     constexpr bool SU = storage_units<ST, RS, ROOT>();
     const Real su = SU ? a.inv_scale : Real(1);  // physical value -> storage units
     const int rest32 = RS ? a.rest32 : 0;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int x, y;
+    if (!node_of<ROW>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
     const int z = blockIdx.z;
-    if (x >= a.nx || y >= a.ny) return;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int nxy = nx * ny;
     const int k = z * nxy + y * nx + x;
@@ -703,10 +702,9 @@ static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<
 template <class ST, int UM, bool ABB>
 __global__ __launch_bounds__(256) void k_adjoint(const StepArgs<typename Store<ST>::Real> a) {
     using Real = typename Store<ST>::Real;
-    const int x = blockIdx.x * blockDim.x + threadIdx.x;
-    const int y = blockIdx.y * blockDim.y + threadIdx.y;
+    int x, y;
+    if (!node_of<false>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
     const int z = blockIdx.z;
-    if (x >= a.nx || y >= a.ny) return;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int nxy = nx * ny;
     const int k = z * nxy + y * nx + x;
@@ -770,29 +768,32 @@ static hipError_t step_t(const elbm_lattice* h, const void* src, void* dst, doub
     if (h->cfg.root_rho < 0 && !(h->cfg.flags & ELBM_FLAG_SCALAR_KERNEL) &&
         try_launch_vec<ST, UM>(h, a))
         return hipGetLastError();
-    dim3 grid, block;
-    grid_for(h, &grid, &block);
+    const RowGrid rg = grid_for(h);
+    const dim3 grid = rg.grid, block = rg.block;
+    a.rows = rg.rows;
     const bool root = h->cfg.root_rho >= 0, abb = a.abb != 0;
     const bool rs = sizeof(ST) == 2 && (a.rest32 || a.sround);
-    if (rs) {
-        if constexpr (sizeof(ST) == 2) {
-            if (root && abb)
-                hipLaunchKernelGGL((k_step<ST, UM, true, true, true>), grid, block, 0, h->stream, a);
-            else if (root)
-                hipLaunchKernelGGL((k_step<ST, UM, true, false, true>), grid, block, 0, h->stream, a);
-            else if (abb)
-                hipLaunchKernelGGL((k_step<ST, UM, false, true, true>), grid, block, 0, h->stream, a);
-            else
-                hipLaunchKernelGGL((k_step<ST, UM, false, false, true>), grid, block, 0, h->stream, a);
-        }
-    } else if (root && abb) {
-        hipLaunchKernelGGL((k_step<ST, UM, true, true, false>), grid, block, 0, h->stream, a);
-    } else if (root) {
-        hipLaunchKernelGGL((k_step<ST, UM, true, false, false>), grid, block, 0, h->stream, a);
-    } else if (abb) {
-        hipLaunchKernelGGL((k_step<ST, UM, false, true, false>), grid, block, 0, h->stream, a);
+    const auto go = [&](auto row, auto rounding) {
+        constexpr bool ROW = decltype(row)::value, RS = decltype(rounding)::value;
+        if (root && abb)
+            hipLaunchKernelGGL((k_step<ST, UM, true, true, RS, false>), grid, block, 0, h->stream, a);
+        else if (root)
+            hipLaunchKernelGGL((k_step<ST, UM, true, false, RS, false>), grid, block, 0, h->stream, a);
+        else if (abb)
+            hipLaunchKernelGGL((k_step<ST, UM, false, true, RS, false>), grid, block, 0, h->stream, a);
+        else
+            hipLaunchKernelGGL((k_step<ST, UM, false, false, RS, ROW>), grid, block, 0, h->stream, a);
+    };
+    // One row per block in scalar registers: 16-bit forms without walls, which are bound by VALU
+    // issue (4-9 % faster on rows of 186 to 341 nodes). FP32 and FP64 are not, and lose 1 % to it;
+    // between walls the scalar work it adds per reflected direction loses 7 %.
+    if constexpr (sizeof(ST) == 2) {
+        if (rs && rg.rows == 1) go(std::true_type{}, std::true_type{});
+        else if (rs) go(std::false_type{}, std::true_type{});
+        else if (rg.rows == 1) go(std::true_type{}, std::false_type{});
+        else go(std::false_type{}, std::false_type{});
     } else {
-        hipLaunchKernelGGL((k_step<ST, UM, false, false, false>), grid, block, 0, h->stream, a);
+        go(std::false_type{}, std::false_type{});
     }
     return hipGetLastError();
 }
@@ -819,8 +820,9 @@ static hipError_t adj_t(const elbm_lattice* h, const void* state, double src_mul
     a.adj_in = static_cast<const Real*>(adj_in);
     a.adj_out = static_cast<Real*>(adj_out);
     a.t_grad = static_cast<Real*>(t_grad);
-    dim3 grid, block;
-    grid_for(h, &grid, &block, 256);  // gathers and local writes: rows may be split
+    const RowGrid rg = grid_for(h, 256);  // gathers and local writes: rows may be split
+    const dim3 grid = rg.grid, block = rg.block;
+    a.rows = rg.rows;
     if (a.abb)
         hipLaunchKernelGGL((k_adjoint<ST, UM, true>), grid, block, 0, h->stream, a);
     else
