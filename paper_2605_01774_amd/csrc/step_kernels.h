@@ -649,36 +649,67 @@ static void launch_vec_w(const elbm_lattice* h, const StepArgs<typename Store<ST
     }
 }
 
-// Nodes per lane chosen when the flags set no width (0: one-node-per-thread kernel), the
-// fastest measured on MI355X (256^3 decay with uniform coefficients, 384^3 porous with a
-// per-node tensor field or material table, 512^3 with per-node tensor, velocity and source
-// fields; same-box sweeps):
-//  - 16-bit forms: 4 nodes (8 bytes) per lane, 2 with a velocity field (4 nodes: 34 %
-//    slower there, 1 node: 1-6 %); on 384-node rows this halves to 2;
-//  - FP32: 1 node per lane (field workload: 4.16 vs 4.27 ms with 2), except on 384-node
-//    rows, where 1 would make a block of 6 wavefronts: there 2 (3 wavefronts; porous 384^3
-//    1.0 % faster with the material table, 1.5 % with the tensor field, same box);
-//  - FP64: 1 node per lane with uniform coefficients, 2 with a per-node tensor or velocity
-//    (porous: 3.02 vs 3.75 ms; field workload: 10.1 ms, against 12.1 ms with 1 and
-//    11.0 ms for the one-node-per-thread kernel).
-// A return of 0 would select the one-node-per-thread kernel.
-template <class ST>
-static int auto_vector_width(bool tfield, bool ufield, int nx) {
-    if (sizeof(ST) == 2) return ufield ? 2 : 4;
+// Nodes per lane of the row-vector kernel when the flags set no width, 0 for the
+// one-node-per-thread kernel. From same-box sweeps of every width and both kernels over rows of
+// 64 to 512 nodes (64^3 to 256^3, 320 x 160^2, 384 x 192^2, 448 x 192 x 160, 512 x 256 x 128),
+// every form, u = 0, uniform and per-node velocity, uniform and per-node tensor and material
+// table; us per step, "n" is the one-node-per-thread kernel:
+//  - 16-bit forms: 4 nodes (8 bytes) per lane (decay 256^3 BF16 V1 218, V2 214, V4 210); 2 with a
+//    velocity field (256^3 V4 376, V2 333) or a tensor field at u = 0 (294 -> 272), 1 with a tensor
+//    field and a uniform velocity (256^3 BF16 V4 321, V2 296, V1 279; BF16 + rest + SR 348 -> 311);
+//  - FP32: 1, but 2 on 384-node rows, where 1 would make blocks of 6 wavefronts;
+//  - FP64: at u = 0, 2 with a tensor (porous 384^3: V1 3750, V2 3020) and on rows of 384 and 512
+//    (844 -> 769, 932 -> 828), else 1; with a uniform velocity 1 (two nodes need 256 to 380 VGPRs,
+//    one or two waves per SIMD: tensor field 128^3 V2 136, V1 112, D3Q27 185 -> 158); with a
+//    velocity field 2 (512^3: V1 12.1 ms, V2 10.1), in D3Q27 1 on rows over 256 (512 x 256 x 128:
+//    V2 2344, V1 2083).
+// The one-node-per-thread kernel where the row-vector kernel's blocks fit a CU badly: one row
+// of 5 to 7 wavefronts does not spread evenly over four SIMDs and waits at its barrier, which
+// costs the kernels most that keep few waves resident:
+//  - FP64, uniform velocity and tensor, 5 wavefronts or more (320: 618, n 468; 384: 989, n 791;
+//    512: 1053, n 952), 5 with a tensor field (560, n 512); u = 0, 5 (515, n 432) and, except with
+//    a tensor field, 7 (848, n 767); D3Q27 with a velocity field up to 256 (256^3: 2347, n 1940);
+//  - FP32 with a velocity field, 5 wavefronts (324, n 284);
+//  - plain 16-bit forms without per-node tensor and velocity, 5 to 7 (320: 154, n 129; 448: 232,
+//    n 193), in D3Q27 also with FP32 rest or stochastic rounding (323, n 254), and there with a
+//    uniform velocity on 384-node rows (BF16 488, n 378);
+//  - plain 16-bit forms between walls at one node per lane (64^3: 20.3, n 8.5; 192^3: 132, n 113),
+//    the rounding forms on 64-node rows (21.6, n 10.4): their wall lanes store single 16-bit
+//    values in a branch per direction.
+template <class ST, int UM>
+static int preferred_width(const elbm_lattice* h) {
+    const int nx = h->cfg.nx;
+    const bool tensor = h->t_field_mode != 0, tnode = h->t_field_mode == 1;
+    if (sizeof(ST) == 2) return UM == 2 ? 2 : (tnode ? (UM == 1 ? 1 : 2) : 4);
     if (sizeof(ST) == 4) return nx == 6 * 64 ? 2 : 1;
-    return (tfield || ufield) ? 2 : 1;
+    if (UM == 2) return Q == 27 ? 1 : 2;
+    if (UM == 1) return 1;
+    return tensor || (Q == 19 && nx > 320) ? 2 : 1;
+}
+template <class ST, int UM>
+static bool prefer_one_node(const elbm_lattice* h, int V, int W, bool rs) {
+    const bool tnode = h->t_field_mode == 1, walls = h->cfg.bc_x == ELBM_DIRICHLET;
+    if (sizeof(ST) == 8) {
+        if (UM == 2) return Q == 27 && h->cfg.nx <= 256;
+        if (UM == 1) return tnode ? W == 5 : W >= 5;
+        return W == 5 || (Q == 19 && W == 7 && !tnode);
+    }
+    if (sizeof(ST) == 4) return UM == 2 && W == 5;
+    if (walls && V == 1 && (!rs || W == 1)) return true;
+    if (tnode || UM == 2) return false;
+    if (Q == 27 && UM == 1 && V == 2 && W == 3) return true;
+    return W >= 5 && W <= 7 && (!rs || Q == 27);
 }
 
 // Row-vector launch if the row shape allows it: nx = 64 V W with 1 <= W <= 8;
-// (flags >> 4) & 0xF sets the width. Without an explicit width, auto_vector_width's choice,
-// or the nearest width (smaller first) that fits the row.
+// (flags >> 4) & 0xF sets the width. Without an explicit width, preferred_width's choice, or
+// the nearest width (smaller first) that fits the row, unless prefer_one_node.
 template <class ST, int UM>
 static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a) {
     const int nx = h->cfg.nx;
     int V = (h->cfg.flags >> ELBM_VECTOR_WIDTH_SHIFT) & 0xF;
     if (V == 0) {
-        const int pref = auto_vector_width<ST>(a.tfield != nullptr, a.ufield != nullptr, nx);
-        if (pref == 0) return false;
+        const int pref = preferred_width<ST, UM>(h);
         const int vmax = sizeof(ST) == 8 ? 2 : 4;
         const int order[5] = {pref, pref / 2, pref / 4, pref * 2, pref * 4};
         for (int c : order) {
@@ -686,7 +717,8 @@ static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<
             V = c;
             break;
         }
-        if (V == 0) return false;
+        if (V == 0 || prefer_one_node<ST, UM>(h, V, nx / (64 * V), sizeof(ST) == 2 && (a.rest32 || a.sround)))
+            return false;
     }
     if (sizeof(ST) == 8 && V > 2) return false;
     if (V != 1 && V != 2 && V != 4) return false;
