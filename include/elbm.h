@@ -35,7 +35,8 @@
  * Ownership: the caller allocates and frees every population buffer, field store, record
  * and adjoint buffer; the library never frees caller memory. The library owns the handle
  * and a small device scratch area (reduction partials, step counters, flags; about 200 KB)
- * allocated at creation.
+ * allocated at creation; the first elbm_reduce or elbm_min_population also pins 4 KB of host
+ * memory for the results of all handles.
  *
  * Streams: all work is enqueued on the stream set by elbm_set_stream (default: the null
  * stream). Calls documented as synchronous wait for that stream.

@@ -224,6 +224,49 @@ void* scratch_of(int device) {
     return (device >= 0 && device < kMaxDevices) ? g_scratch_dev[device] : nullptr;
 }
 
+// Pinned host memory that a handle's synchronous reductions write their result to: a slot of
+// one small slab, allocated at the first such call and kept until the process ends, so that
+// creating and destroying lattices does not pin and unpin pages (about 80 us); slots go back
+// when their handle is destroyed. A handle that finds none free pins memory of its own.
+constexpr int kResultSlots = 64, kResultDoubles = 8;  // one 64-byte line per slot
+std::mutex g_result_mu;
+double* g_result_slab = nullptr;
+uint64_t g_result_used = 0;
+
+int acquire_result(elbm_lattice* h) {
+    if (h->h_out) return ELBM_OK;
+    std::lock_guard<std::mutex> lock(g_result_mu);
+    void* p = nullptr;
+    if (!g_result_slab) {
+        HIP_OK(hipHostMalloc(&p, sizeof(double) * kResultDoubles * kResultSlots, hipHostMallocPortable), "hipHostMalloc");
+        g_result_slab = static_cast<double*>(p);
+    }
+    for (int s = 0; s < kResultSlots; ++s)
+        if (!(g_result_used >> s & 1)) {
+            g_result_used |= uint64_t(1) << s;
+            h->h_out = g_result_slab + kResultDoubles * s;
+            h->h_slot = s;
+            return ELBM_OK;
+        }
+    HIP_OK(hipHostMalloc(&p, sizeof(double) * kResultDoubles, hipHostMallocPortable), "hipHostMalloc");
+    h->h_out = static_cast<double*>(p);
+    h->h_slot = -1;
+    return ELBM_OK;
+}
+
+// No call of the handle is in flight when it is destroyed, and its reductions waited for their
+// result, so nothing writes to the slot any more.
+void release_result(elbm_lattice* h) {
+    if (!h->h_out) return;
+    if (h->h_slot < 0) {
+        (void)hipHostFree(h->h_out);
+    } else {
+        std::lock_guard<std::mutex> lock(g_result_mu);
+        g_result_used &= ~(uint64_t(1) << h->h_slot);
+    }
+    h->h_out = nullptr;
+}
+
 }  // namespace
 
 extern "C" {
@@ -286,8 +329,8 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     long long nb = (n + 255) / 256;
     h->part_blocks = int(nb < kMaxPartBlocks ? nb : kMaxPartBlocks);
     if (h->part_blocks < 1) h->part_blocks = 1;
-    const size_t bytes = sizeof(double) * (4 * (size_t)h->part_blocks + 8) + kCntWords * sizeof(unsigned long long) +
-                         sizeof(long long);
+    const size_t bytes = sizeof(double) * 4 * (size_t)h->part_blocks + kCntWords * sizeof(unsigned long long) +
+                         sizeof(long long) + sizeof(unsigned long long);
     void* scratch = nullptr;
     e = hipMalloc(&scratch, bytes);
     if (e != hipSuccess) {
@@ -295,9 +338,11 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
         return hip_fail(e, "hipMalloc scratch");
     }
     h->d_part = static_cast<double*>(scratch);
-    h->d_cnt = reinterpret_cast<unsigned long long*>(h->d_part + 4 * h->part_blocks + 8);
+    h->d_cnt = reinterpret_cast<unsigned long long*>(h->d_part + 4 * h->part_blocks);
     h->d_flag = reinterpret_cast<long long*>(h->d_cnt + kCntWords);
-    e = hipMemset(h->d_cnt, 0, kCntWords * sizeof(unsigned long long));
+    h->d_ticket = reinterpret_cast<unsigned long long*>(h->d_flag + 1);
+    // counters, flag and ticket start at zero
+    e = hipMemset(h->d_cnt, 0, (kCntWords + 2) * sizeof(unsigned long long));
     if (e != hipSuccess) {
         (void)hipFree(scratch);
         delete h;
@@ -312,6 +357,7 @@ int elbm_destroy(elbm_lattice* h) {
     if (!h) return ELBM_OK;
     (void)hipSetDevice(h->device);
     if (h->d_part) (void)hipFree(h->d_part);
+    release_result(h);
     delete h;
     return ELBM_OK;
 }
@@ -619,10 +665,11 @@ int elbm_reduce(elbm_lattice* h, double* out4) {
     if (!h->initialized) return fail(ELBM_ESTATE, "lattice not initialised");
     if (!h->t_set) return fail(ELBM_ESTATE, "diffusion tensor not set");
     if (int r = set_device(h)) return r;
-    double* dout = h->d_part + 4 * h->part_blocks;
-    HIP_OK(launch_reduce(h, dout, h->d_part), "reduce");
-    HIP_OK(hipMemcpyAsync(out4, dout, 4 * sizeof(double), hipMemcpyDeviceToHost, h->stream), "reduce copy");
+    // the kernel writes the sums to pinned host memory itself: no copy, one wait
+    if (int r = acquire_result(h)) return r;
+    HIP_OK(launch_reduce(h, h->h_out, h->d_part), "reduce");
     HIP_OK(hipStreamSynchronize(h->stream), "reduce sync");
+    for (int m = 0; m < 4; ++m) out4[m] = h->h_out[m];
     return ELBM_OK;
 }
 
@@ -647,10 +694,10 @@ int elbm_min_population(elbm_lattice* h, double* out) {
     if (!out) return fail(ELBM_EINVAL, "null output");
     if (!h->initialized) return fail(ELBM_ESTATE, "lattice not initialised");
     if (int r = set_device(h)) return r;
-    double* dout = h->d_part + 4 * h->part_blocks + 4;  // past the four sums of elbm_reduce
-    HIP_OK(launch_min_population(h, dout), "min population");
-    HIP_OK(hipMemcpyAsync(out, dout, sizeof(double), hipMemcpyDeviceToHost, h->stream), "min population copy");
+    if (int r = acquire_result(h)) return r;
+    HIP_OK(launch_min_population(h, h->h_out), "min population");
     HIP_OK(hipStreamSynchronize(h->stream), "min population sync");
+    *out = h->h_out[0];
     return ELBM_OK;
 }
 

@@ -190,14 +190,16 @@ __device__ inline double eq_factor(int i, const double u[3]) {
     return 1.0 + 3.0 * cu + 4.5 * cu * cu - 1.5 * uu;
 }
 
-// Row and column of node k (x fastest): the population buffers are addressed by row.
+// Row and column of node k (x fastest): the population buffers are addressed by row. Node
+// indices stay below 2^31, so the division is a 32-bit one (the 64-bit one was a third of the
+// readout's instructions).
 struct RowCol {
     long long r;
     int x;
 };
 __device__ inline RowCol row_col(long long k, int nx) {
-    const long long r = k / nx;
-    return {r, int(k - r * nx)};
+    const unsigned r = unsigned(k) / unsigned(nx);
+    return {(long long)r, int(unsigned(k) - r * unsigned(nx))};
 }
 
 // Store the Q FP64 values v (deviations) of node k into a population buffer. With the
@@ -212,6 +214,7 @@ __device__ inline void put_node(const StepArgs<typename Store<ST>::Real>& a, ST*
     if constexpr (sizeof(ST) == 2) {
         if (a.rest32) {
             double res = 0.0;
+#pragma unroll
             for (int i = 1; i < Q; ++i) {
                 const float q = quantize16<ST>(float(v[i]), 0u, false, a.scale, a.inv_scale);
                 res += v[i] - double(q);
@@ -221,22 +224,30 @@ __device__ inline void put_node(const StepArgs<typename Store<ST>::Real>& a, ST*
             return;
         }
     }
+#pragma unroll
     for (int i = 0; i < Q; ++i) pop_put<ST>(buf, i, p.r, p.x, a.nx, Real(v[i]), a.rest32, a.inv_scale);
 }
 
-template <class ST>
+// Initial state (MODE 0: u = 0 and no initial flux, where every E_i is 1 and the flux lift 0).
+template <class ST, int MODE>
 __global__ void k_init(StepArgs<typename Store<ST>::Real> a, int umode, const double* phi0,
                        const double* j0) {
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
-    double u[3];
-    node_u64(a, umode, k, u);
     const double p = phi0[k];
-    const double jx = j0 ? j0[k] : 0.0, jy = j0 ? j0[a.n + k] : 0.0, jz = j0 ? j0[2 * a.n + k] : 0.0;
     double g[Q];
-    for (int i = 0; i < Q; ++i)
-        g[i] = weight(i) * (p * eq_factor(i, u) - double(a.phi_ref)) +
-               w3(i) * (cx(i) * jx + cy(i) * jy + cz(i) * jz);
+    if constexpr (MODE == 0) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) g[i] = weight(i) * (p - double(a.phi_ref));
+    } else {
+        double u[3];
+        node_u64(a, umode, k, u);
+        const double jx = j0 ? j0[k] : 0.0, jy = j0 ? j0[a.n + k] : 0.0, jz = j0 ? j0[2 * a.n + k] : 0.0;
+#pragma unroll
+        for (int i = 0; i < Q; ++i)
+            g[i] = weight(i) * (p * eq_factor(i, u) - double(a.phi_ref)) +
+                   w3(i) * (cx(i) * jx + cy(i) * jy + cz(i) * jz);
+    }
     put_node<ST>(a, static_cast<ST*>(a.dst), k, g);
 }
 
@@ -250,6 +261,7 @@ __global__ void k_init_grad(StepArgs<typename Store<ST>::Real> a, int umode,
     double u[3];
     node_u64(a, umode, k, u);
     double gp = 0.0, gj[3] = {0.0, 0.0, 0.0};
+#pragma unroll
     for (int i = 0; i < Q; ++i) {
         const double g = double(adj[(size_t)i * a.n + k]);
         gp += weight(i) * eq_factor(i, u) * g;
@@ -271,6 +283,7 @@ __global__ void k_fill_adjoint(const double* dphi, long long n, Real* adj) {
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= n) return;
     const Real v = Real(dphi[k]);
+#pragma unroll
     for (int i = 0; i < Q; ++i) adj[(size_t)i * n + k] = v;
 }
 
@@ -291,6 +304,7 @@ __global__ void k_flush(StepArgs<typename Store<ST>::Real> a, int umode) {
     ST* buf = static_cast<ST*>(a.dst);
     const RowCol p = row_col(k, a.nx);
     double v[Q];
+#pragma unroll
     for (int i = 0; i < Q; ++i)
         v[i] = double(pop_load<ST>(buf, i, p.r, p.x, a.nx, a.rest32, a.scale)) + R * weight(i) * eq_factor(i, u);
     put_node<ST>(a, buf, k, v);
@@ -305,6 +319,7 @@ __global__ void k_get_pops(StepArgs<typename Store<ST>::Real> a, int umode, doub
     const double R = pending_r(a, k);
     const ST* buf = static_cast<const ST*>(a.src);
     const RowCol p = row_col(k, a.nx);
+#pragma unroll
     for (int i = 0; i < Q; ++i)
         f[(size_t)i * a.n + k] = weight(i) * double(a.phi_ref) +
                                  double(pop_load<ST>(buf, i, p.r, p.x, a.nx, a.rest32, a.scale)) +
@@ -316,35 +331,49 @@ __global__ void k_set_pops(StepArgs<typename Store<ST>::Real> a, const double* f
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     double v[Q];
+#pragma unroll
     for (int i = 0; i < Q; ++i) v[i] = f[(size_t)i * a.n + k] - weight(i) * double(a.phi_ref);
     put_node<ST>(a, static_cast<ST*>(a.dst), k, v);
 }
 
-// phi deviation and LB flux q = T j / 2 of one node, FP64, including the pending source.
+// phi deviation and LB flux q = T j / 2 of one node, FP64, including the pending source. The
+// populations are loaded before anything is computed, and the pending source's equilibrium
+// factors only where a source is pending.
 template <class ST>
 __device__ inline void node_moments(const StepArgs<typename Store<ST>::Real>& a, int umode, long long k,
                                     double* dphi, double q[3]) {
+    using Real = typename Store<ST>::Real;
+    const ST* buf = static_cast<const ST*>(a.src);
+    const RowCol p = row_col(k, a.nx);
+    Real v[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) v[i] = pop_load<ST>(buf, i, p.r, p.x, a.nx, a.rest32, a.scale);
     double u[3];
     node_u64(a, umode, k, u);
     const double R = pending_r(a, k);
-    const ST* buf = static_cast<const ST*>(a.src);
-    const RowCol p = row_col(k, a.nx);
+    double T[6];
+    const long long row = tensor_row(a, k);
+#pragma unroll
+    for (int m = 0; m < 6; ++m) T[m] = a.tfield ? double(a.tfield[6 * row + m]) : double(a.T[m]);
+    double d[Q];
+#pragma unroll
+    for (int i = 0; i < Q; ++i) d[i] = double(v[i]);
+    if (a.has_src && a.src_mult != Real(0)) {
+#pragma unroll
+        for (int i = 0; i < Q; ++i) d[i] += R * weight(i) * eq_factor(i, u);
+    }
     double s = 0.0, j0 = 0.0, j1 = 0.0, j2 = 0.0;
+#pragma unroll
     for (int i = 0; i < Q; ++i) {
-        const double d = double(pop_load<ST>(buf, i, p.r, p.x, a.nx, a.rest32, a.scale)) +
-                         R * weight(i) * eq_factor(i, u);
-        s += d;
-        j0 += cx(i) * d;
-        j1 += cy(i) * d;
-        j2 += cz(i) * d;
+        s += d[i];
+        if (cx(i)) j0 += cx(i) * d[i];
+        if (cy(i)) j1 += cy(i) * d[i];
+        if (cz(i)) j2 += cz(i) * d[i];
     }
     const double phi = double(a.phi_ref) + s;
     j0 -= phi * u[0];
     j1 -= phi * u[1];
     j2 -= phi * u[2];
-    double T[6];
-    const long long row = tensor_row(a, k);
-    for (int m = 0; m < 6; ++m) T[m] = a.tfield ? double(a.tfield[6 * row + m]) : double(a.T[m]);
     q[0] = 0.5 * (T[0] * j0 + T[1] * j1 + T[2] * j2);
     q[1] = 0.5 * (T[1] * j0 + T[3] * j1 + T[4] * j2);
     q[2] = 0.5 * (T[2] * j0 + T[4] * j1 + T[5] * j2);
@@ -357,48 +386,99 @@ __global__ void k_moments(StepArgs<typename Store<ST>::Real> a, int umode, doubl
     if (k >= a.n) return;
     double dphi, q[3];
     node_moments<ST>(a, umode, k, &dphi, q);
-    if (phi) phi[k] = double(a.phi_ref) + dphi;
+    if (phi) __builtin_nontemporal_store(double(a.phi_ref) + dphi, phi + k);
     if (q3) {
-        q3[k] = q[0];
-        q3[a.n + k] = q[1];
-        q3[2 * a.n + k] = q[2];
+        __builtin_nontemporal_store(q[0], q3 + k);
+        __builtin_nontemporal_store(q[1], q3 + a.n + k);
+        __builtin_nontemporal_store(q[2], q3 + 2 * a.n + k);
     }
 }
 
-// Neumaier-compensated accumulation per thread (grid-stride), then an FP64 block tree.
+// Global sums: Neumaier-compensated accumulation per thread (grid-stride), then an FP64 sum over
+// the block, and the sum over the blocks by the block that finishes last, in the same launch.
+// A second launch of one block took 3.8 us after a first of 10.4 at 32^3.
 constexpr int kRedThreads = 256;
 
+__device__ inline void neumaier(double& sum, double& comp, double v) {
+    const double t = sum + v;
+    comp += (fabs(sum) >= fabs(v)) ? (sum - t) + v : (v - t) + sum;
+    sum = t;
+}
+
+// Sum (MIN: minimum) of one value per thread over a block of kRedThreads, in thread 0: within the
+// wavefronts by lane shuffles, across them through LDS (`sh`: one value per wavefront).
+template <bool MIN>
+__device__ inline double block_reduce(double v, double* sh) {
+#pragma unroll
+    for (int o = 32; o > 0; o >>= 1) {
+        const double w = __shfl_down(v, o);
+        v = MIN ? fmin(v, w) : v + w;
+    }
+    __syncthreads();  // sh may hold an earlier reduction's values
+    if ((threadIdx.x & 63) == 0) sh[threadIdx.x >> 6] = v;
+    __syncthreads();
+    v = sh[0];
+#pragma unroll
+    for (int w = 1; w < kRedThreads / 64; ++w) v = MIN ? fmin(v, sh[w]) : v + sh[w];
+    return v;
+}
+
+// Whether this block is the last of its launch to get here; what the others wrote before is
+// then visible to it. The ticket counts blocks over all launches and is never reset, so that it
+// stays in step whatever runs between two launches; every launch with it has gridDim.x blocks.
+__device__ inline bool last_block(unsigned long long* ticket, int* flag) {
+    if (threadIdx.x == 0) {
+        const unsigned long long t = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
+        *flag = (t + 1) % gridDim.x == 0;
+    }
+    __syncthreads();
+    return *flag != 0;
+}
+
 template <class ST>
-__global__ __launch_bounds__(kRedThreads) void k_reduce_partial(StepArgs<typename Store<ST>::Real> a,
-                                                                int umode, double* part) {
+__global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<ST>::Real> a, int umode,
+                                                        double* part, unsigned long long* ticket, double add_mass,
+                                                        double* out) {
+    __shared__ double sh[kRedThreads / 64];
+    __shared__ int last;
     double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0};
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < a.n;
          k += (long long)gridDim.x * blockDim.x) {
         double v[4];
         node_moments<ST>(a, umode, k, &v[0], &v[1]);
-        for (int m = 0; m < 4; ++m) {
-            const double t = sum[m] + v[m];
-            comp[m] += (fabs(sum[m]) >= fabs(v[m])) ? (sum[m] - t) + v[m] : (v[m] - t) + sum[m];
-            sum[m] = t;
-        }
+#pragma unroll
+        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], v[m]);
     }
-    __shared__ double sh[4][kRedThreads];
-    for (int m = 0; m < 4; ++m) sh[m][threadIdx.x] = sum[m] + comp[m];
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int m = 0; m < 4; ++m) sh[m][threadIdx.x] += sh[m][threadIdx.x + s];
-        __syncthreads();
+    double r[4];
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int m = 0; m < 4; ++m) part[4 * blockIdx.x + m] = r[m];
     }
-    if (threadIdx.x == 0)
-        for (int m = 0; m < 4; ++m) part[4 * blockIdx.x + m] = sh[m][0];
+    if (!last_block(ticket, &last)) return;
+    // each thread takes a strided subset of the block partials
+#pragma unroll
+    for (int m = 0; m < 4; ++m) sum[m] = comp[m] = 0.0;
+    for (int b = threadIdx.x; b < int(gridDim.x); b += kRedThreads)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], part[4 * b + m]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
+    if (threadIdx.x == 0) {
+        out[0] = add_mass + r[0];
+#pragma unroll
+        for (int m = 1; m < 4; ++m) out[m] = r[m];
+    }
 }
 
 // Smallest current population g_i (full value, as the population readout gives it, with
 // the pending source half-step) per block, grid-stride; NaN values are skipped by fmin.
 template <class ST>
-__global__ __launch_bounds__(kRedThreads) void k_min_partial(StepArgs<typename Store<ST>::Real> a,
-                                                             int umode, double* part) {
+__global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>::Real> a, int umode, double* part,
+                                                     unsigned long long* ticket, double* out) {
+    __shared__ double sh[kRedThreads / 64];
+    __shared__ int last;
     double m = __builtin_huge_val();
     const ST* buf = static_cast<const ST*>(a.src);
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < a.n;
@@ -407,58 +487,19 @@ __global__ __launch_bounds__(kRedThreads) void k_min_partial(StepArgs<typename S
         node_u64(a, umode, k, u);
         const double R = pending_r(a, k);
         const RowCol p = row_col(k, a.nx);
+#pragma unroll
         for (int i = 0; i < Q; ++i)
             m = fmin(m, weight(i) * double(a.phi_ref) +
                             double(pop_load<ST>(buf, i, p.r, p.x, a.nx, a.rest32, a.scale)) +
                             R * weight(i) * eq_factor(i, u));
     }
-    __shared__ double sh[kRedThreads];
-    sh[threadIdx.x] = m;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) part[blockIdx.x] = sh[0];
-}
-
-__global__ __launch_bounds__(kRedThreads) void k_min_final(const double* part, int nb, double* out) {
-    double m = __builtin_huge_val();
-    for (int b = threadIdx.x; b < nb; b += blockDim.x) m = fmin(m, part[b]);
-    __shared__ double sh[kRedThreads];
-    sh[threadIdx.x] = m;
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s) sh[threadIdx.x] = fmin(sh[threadIdx.x], sh[threadIdx.x + s]);
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) out[0] = sh[0];
-}
-
-// One block of kRedThreads threads: each thread sums a strided subset of the block
-// partials with Neumaier compensation, then the threads' results are added in a tree.
-__global__ __launch_bounds__(kRedThreads) void k_reduce_final(const double* part, int nb,
-                                                              double add_mass, double* out) {
-    double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0};
-    for (int b = threadIdx.x; b < nb; b += blockDim.x)
-        for (int m = 0; m < 4; ++m) {
-            const double v = part[4 * b + m];
-            const double t = sum[m] + v;
-            comp[m] += (fabs(sum[m]) >= fabs(v)) ? (sum[m] - t) + v : (v - t) + sum[m];
-            sum[m] = t;
-        }
-    __shared__ double sh[4][kRedThreads];
-    for (int m = 0; m < 4; ++m) sh[m][threadIdx.x] = sum[m] + comp[m];
-    __syncthreads();
-    for (int s = kRedThreads / 2; s > 0; s >>= 1) {
-        if (threadIdx.x < s)
-            for (int m = 0; m < 4; ++m) sh[m][threadIdx.x] += sh[m][threadIdx.x + s];
-        __syncthreads();
-    }
-    if (threadIdx.x == 0) {
-        out[0] = add_mass + sh[0][0];
-        for (int m = 1; m < 4; ++m) out[m] = sh[m][0];
-    }
+    m = block_reduce<true>(m, sh);
+    if (threadIdx.x == 0) part[blockIdx.x] = m;
+    if (!last_block(ticket, &last)) return;
+    m = __builtin_huge_val();
+    for (int b = threadIdx.x; b < int(gridDim.x); b += kRedThreads) m = fmin(m, part[b]);
+    m = block_reduce<true>(m, sh);
+    if (threadIdx.x == 0) out[0] = m;
 }
 
 // dL/dT (6 stored components) -> dL/dD or dL/dL (6 stored components), FP64.
@@ -576,7 +617,10 @@ hipError_t launch_init(const elbm_lattice* h, const double* phi0, const double* 
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, 0.0);
         a.dst = dst;
-        hipLaunchKernelGGL(k_init<ST>, dim3(nb), dim3(256), 0, h->stream, a, h->u_mode, phi0, j0);
+        if (h->u_mode == 0 && !j0)
+            hipLaunchKernelGGL((k_init<ST, 0>), dim3(nb), dim3(256), 0, h->stream, a, h->u_mode, phi0, j0);
+        else
+            hipLaunchKernelGGL((k_init<ST, 1>), dim3(nb), dim3(256), 0, h->stream, a, h->u_mode, phi0, j0);
     });
     return hipGetLastError();
 }
@@ -644,28 +688,25 @@ hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const elbm_lattice* h, double* out4_dev, double* part) {
+hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part) {
     const int nb = h->part_blocks;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
-        hipLaunchKernelGGL(k_reduce_partial<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a,
-                           h->u_mode, part);
+        hipLaunchKernelGGL(k_reduce<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, part,
+                           h->d_ticket, double(h->n) * h->cfg.phi_ref, out4);
     });
-    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedThreads), 0, h->stream, part, nb,
-                       double(h->n) * h->cfg.phi_ref, out4_dev);
     return hipGetLastError();
 }
 
-hipError_t launch_min_population(const elbm_lattice* h, double* out_dev) {
+hipError_t launch_min_population(const elbm_lattice* h, double* out) {
     const int nb = h->part_blocks;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
-        hipLaunchKernelGGL(k_min_partial<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a,
-                           h->u_mode, h->d_part);
+        hipLaunchKernelGGL(k_min<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, h->d_part,
+                           h->d_ticket, out);
     });
-    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kRedThreads), 0, h->stream, h->d_part, nb, out_dev);
     return hipGetLastError();
 }
 
