@@ -74,9 +74,9 @@ extern "C" {
 
 /* elbm_config.flags */
 #define ELBM_FLAG_SCALAR_KERNEL 1 /* always use the one-node-per-thread step kernel. By
-                                     default rows of nx = 64 V W nodes (W <= 8) use the
-                                     row-vector kernel (V nodes per lane), other rows the
-                                     one-node-per-thread kernel; elbm_step and
+                                     default most rows of nx = 64 V W nodes (W <= 8) use
+                                     the row-vector kernel (V nodes per lane), other rows
+                                     the one-node-per-thread kernel; elbm_step and
                                      elbm_step_record may take two steps per launch where
                                      that is faster; results are bitwise equal. */
 #define ELBM_VECTOR_WIDTH_SHIFT 4 /* (flags >> 4) & 0xF: nodes per lane V in {1, 2, 4} of

@@ -33,7 +33,8 @@ struct StepArgs {
     int sround;     // 16-bit forms: stochastic rounding of the stores
     uint32_t tmix;  // hash of the time step, mixed into the rounding counters
     int xcd_remap;  // row-vector kernel: XCD slab block order (xcd_block)
-    int rows;       // one-node-per-thread kernels: x-rows of a block
+    int rows;       // one-node-per-thread kernels, ragged row-vector: x-rows of a block
+    int waves;      // row-vector kernel on ragged rows: wavefronts of a row
     float inv_nx;   // 1 / nx, for blocks of several rows
     Real* lam_rec;
     uint8_t* br_rec;
@@ -203,6 +204,7 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
     a.tmix = step_mix(h->time);
     a.xcd_remap = 0;
     a.rows = 1;
+    a.waves = 1;
     a.inv_nx = 1.0f / float(h->cfg.nx);
     a.phi_lo = Real(h->phi_lo);
     a.phi_hi = Real(h->phi_hi);

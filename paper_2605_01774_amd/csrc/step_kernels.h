@@ -244,8 +244,11 @@ struct VecIO {
         }
     }
 
+    template <bool NT = true>
     __device__ static inline void load(const ST* p, Real (&out)[V], Real scale) {
-        const Raw raw = __builtin_nontemporal_load(reinterpret_cast<const Raw*>(p));
+        Raw raw;
+        if constexpr (NT) raw = __builtin_nontemporal_load(reinterpret_cast<const Raw*>(p));
+        else raw = *reinterpret_cast<const Raw*>(p);
         if constexpr (BYTES == 2) {
             out[0] = from16(uint32_t(raw), scale);
         } else {
@@ -264,6 +267,7 @@ struct VecIO {
         }
     }
 
+    template <bool NT = true>
     __device__ static inline void store(ST* p, const Real (&in)[V], Real inv_scale) {
         Raw raw;
         if constexpr (BYTES == 2) {
@@ -285,7 +289,8 @@ struct VecIO {
             }
             __builtin_memcpy(&raw, w, sizeof(w));
         }
-        __builtin_nontemporal_store(raw, reinterpret_cast<Raw*>(p));
+        if constexpr (NT) __builtin_nontemporal_store(raw, reinterpret_cast<Raw*>(p));
+        else *reinterpret_cast<Raw*>(p) = raw;
     }
 };
 
@@ -341,30 +346,47 @@ __device__ inline void xcd_block(unsigned by, unsigned bz, unsigned gy, unsigned
     tz = int((gz >> 3) * (by & 7u) + (bz >> 3));
 }
 
+// W = 0: rows of any length that V divides, in a.waves (1 .. 8) wavefronts. The lanes past the
+// row's end repeat its last V nodes and store nothing; the rotation closes at the last lane
+// with nodes. Such rows start and end inside cache lines, which the next run or row completes:
+// plain accesses there.
 template <class ST, int UM, int V, int W, bool ABB, bool RS>
-__global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArgs<typename Store<ST>::Real> a) {
+__global__ __launch_bounds__(W > 4 ? 64 * W : (W ? 256 : 512)) void k_step_vec(
+    const StepArgs<typename Store<ST>::Real> a) {
     using Real = typename Store<ST>::Real;
     using IO = VecIO<ST, V>;
     constexpr bool SU = storage_units<ST, RS, false>();
     const Real su = SU ? a.inv_scale : Real(1);  // physical value -> storage units
-    constexpr int ROWS = (W == 3 || W > 4) ? 1 : 4 / W;  // rows per block (blockDim.y)
-    // values crossing between the wavefronts of a row: [row][wave][direction]
-    __shared__ Real xfer[ROWS][W > 1 ? W : 1][Q];
+    constexpr bool RAG = W == 0;
+    const int WN = RAG ? a.waves : W;
+    constexpr int FROWS = RAG ? 1 : ((W == 3 || W > 4) ? 1 : 4 / (RAG ? 1 : W));
+    const int ROWS = RAG ? a.rows : FROWS;  // rows per block (blockDim.y)
+    // values crossing between the wavefronts of a row: [row and wave][direction]
+    constexpr int XW = RAG ? 8 : FROWS * W;
+    __shared__ Real xfer[XW][Q];
     const int lane = threadIdx.x & 63;
-    const int w = threadIdx.x >> 6;  // wavefront within the row
+    const int w = RAG ? __builtin_amdgcn_readfirstlane(int(threadIdx.x >> 6)) : threadIdx.x >> 6;  // wavefront within the row
+    // last lane of the wavefront with nodes of the row
+    const int tail = RAG ? min(63, (a.nx - w * 64 * V) / V - 1) : 63;
     // A wavefront lies in one row (blockDim.x is a multiple of 64), so threadIdx.y is uniform
     // across its lanes: read through readfirstlane, the row and every row offset below stay
     // in scalar registers, and each access is a scalar row base plus the lane's column.
-    const int ty = ROWS == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.y));
+    const int ty = !RAG && FROWS == 1 ? 0 : __builtin_amdgcn_readfirstlane(int(threadIdx.y));
     int by, z;
     // the grid is ((ny + ROWS - 1) / ROWS, nz) blocks in y and z (from the arguments, which
     // the wave has already loaded, rather than from the dispatch packet)
-    xcd_block(blockIdx.y, blockIdx.z, unsigned((a.ny + ROWS - 1) / ROWS), unsigned(a.nz), a.xcd_remap != 0, by, z);
+    if constexpr (RAG) {
+        by = int(blockIdx.y);
+        z = int(blockIdx.z);
+    } else {
+        xcd_block(blockIdx.y, blockIdx.z, unsigned((a.ny + FROWS - 1) / FROWS), unsigned(a.nz), a.xcd_remap != 0, by, z);
+    }
     const int y = by * ROWS + ty;
     const bool active = y < a.ny;  // uniform per wavefront
     if (W == 1 && !active) return;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
-    const int xo = (w * 64 + lane) * V;
+    const int xo = (w * 64 + (RAG ? min(lane, tail) : lane)) * V;
+    const bool mine = !RAG || lane <= tail;  // the lane's nodes are its own
     const int r = z * ny + (active ? y : 0);  // row
     const long long kr = (long long)r * nx;   // node index of the row's x = 0
     // FP32 rest population of the 16-bit forms (ELBM_FLAG_REST_FP32)
@@ -383,7 +405,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
     if (ar.br_rec) ar.br_rec += kr;
     // wall lanes of a Dirichlet row: the node at x = 0 and the node at x = nx - 1
     const bool lo_wall = ABB && w == 0 && lane == 0;
-    const bool hi_wall = ABB && w == W - 1 && lane == 63;
+    const bool hi_wall = ABB && w == WN - 1 && lane == tail;
 
     // Per-node fields of the lane's V nodes, issued before the populations (FP64 and 16-bit
     // storage, up to two nodes per lane): loaded node by node after the populations and the
@@ -463,7 +485,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
             bool done = false;
             if constexpr (sizeof(ST) == 2) {
                 if (i == 0 && rest32) {
-                    VecIO<float, V>::load(reinterpret_cast<const float*>(srow) + xo, t, 1.0f);
+                    VecIO<float, V>::template load<!RAG>(reinterpret_cast<const float*>(srow) + xo, t, 1.0f);
                     if constexpr (SU) {
 #pragma unroll
                         for (int e = 0; e < V; ++e) t[e] *= a.inv_scale;
@@ -471,7 +493,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
                     done = true;
                 }
             }
-            if (!done) IO::load(srow + run_offset(i, nx, rest32) + xo, t, SU ? Real(1) : a.scale);
+            if (!done) IO::template load<!RAG>(srow + run_offset(i, nx, rest32) + xo, t, SU ? Real(1) : a.scale);
 #pragma unroll
             for (int e = 0; e < V; ++e) d[e][i] = t[e];
         }
@@ -507,11 +529,11 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
             NodeOut<Real> o;
             collide<Real, UM, false, sizeof(ST) == 4, sizeof(ST) != 2>(d[e], c, a.phi_ref * su, a.eps * su, a.tau2,
                                                                        a.root_rho, post[e], o);
-            if (ar.lam_rec) {
+            if (ar.lam_rec && mine) {
                 ar.lam_rec[xo + e] = o.lam;
                 ar.br_rec[xo + e] = uint8_t(o.branch);
             }
-            if (a.counters) {
+            if (a.counters && mine) {
                 const unsigned slot = blockIdx.y + gridDim.y * blockIdx.z;
                 if (o.branch != 255) atomicAdd(a.counters + cnt_index(0, slot), 1ull);
                 if (!isfinite(o.dphi)) atomicAdd(a.counters + cnt_index(2, slot), 1ull);
@@ -529,16 +551,18 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
             if (SU && rest32) post[e][0] *= a.scale;
         }
     }
-    if constexpr (W > 1) {
+    const int xrow = (RAG || FROWS > 1) ? int(threadIdx.y) * WN : 0;
+    if constexpr (W != 1) {
         // the first and last lane of every wavefront publish the values leaving the wave
-        if (active && (lane == 0 || lane == 63)) {
+        if (active && (lane == 0 || lane == tail)) {
 #pragma unroll
-            for (int i = 1; i < Q; ++i)
-                if (cx(i) > 0 && lane == 63) xfer[threadIdx.y][w][i] = post[V - 1][i];
-                else if (cx(i) < 0 && lane == 0) xfer[threadIdx.y][w][i] = post[0][i];
+            for (int i = 1; i < Q; ++i) {
+                if (cx(i) > 0 && lane == tail) xfer[xrow + w][i] = post[V - 1][i];
+                if (cx(i) < 0 && lane == 0) xfer[xrow + w][i] = post[0][i];
+            }
         }
         __syncthreads();
-        if (!active) return;
+        if (!active || !mine) return;
     }
     // RS: store_rounding leaves the 16-bit values in storage units, stored unscaled
     const Real st_inv = (RS || SU) ? Real(1) : a.inv_scale;
@@ -547,7 +571,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
     const int zm = (z == 0) ? nz - 1 : z - 1, zp = (z == nz - 1) ? 0 : z + 1;
     const int ry[3] = {ym, y, yp};
     const int rz[3] = {zm * ny, z * ny, zp * ny};
-    const int wl = (w == 0) ? W - 1 : w - 1, wr = (w == W - 1) ? 0 : w + 1;
+    const int wl = (w == 0) ? WN - 1 : w - 1, wr = (w == WN - 1) ? 0 : w + 1;
 #pragma unroll
     for (int i = 0; i < Q; ++i) {
         Real out[V];
@@ -556,19 +580,19 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
             for (int e = 0; e < V; ++e) out[e] = post[e][i];
         } else if (cx(i) > 0) {
             out[0] = wave_rotate<1>(post[V - 1][i]);
-            if (W > 1 && lane == 0) out[0] = xfer[threadIdx.y][wl][i];
+            if (W != 1 && lane == 0) out[0] = xfer[xrow + wl][i];
 #pragma unroll
             for (int e = 1; e < V; ++e) out[e] = post[e - 1][i];
         } else {
 #pragma unroll
             for (int e = 0; e < V - 1; ++e) out[e] = post[e + 1][i];
             out[V - 1] = wave_rotate<-1>(post[0][i]);
-            if (W > 1 && lane == 63) out[V - 1] = xfer[threadIdx.y][wr][i];
+            if (W != 1 && lane == tail) out[V - 1] = xfer[xrow + wr][i];
         }
         ST* drow = dst + size_t(rz[cz(i) + 1] + ry[cy(i) + 1]) * re;
         if constexpr (sizeof(ST) == 2) {
             if (i == 0 && rest32) {
-                VecIO<float, V>::store(reinterpret_cast<float*>(drow) + xo, out, 1.0f);
+                VecIO<float, V>::template store<!RAG>(reinterpret_cast<float*>(drow) + xo, out, 1.0f);
                 continue;
             }
         }
@@ -581,7 +605,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : 256) void k_step_vec(const StepArg
             for (int e = 0; e < V; ++e)
                 if (e != skip) Store<ST>::put(p + e, out[e], st_inv);
         } else {
-            IO::store(p, out, st_inv);
+            IO::template store<!RAG>(p, out, st_inv);
         }
     }
     if (ABB && (lo_wall || hi_wall)) {
@@ -633,6 +657,33 @@ static void launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>:
     } else {
         hipLaunchKernelGGL((k_step_vec<ST, UM, V, W, false, false>), grid, block, 0, h->stream, a);
     }
+}
+
+// Rows that no width divides: the 16-bit forms with FP32 rest or stochastic rounding at u = 0,
+// two nodes per lane, up to 1024 nodes, where at least three quarters of the lanes have nodes:
+// 4-37 % faster than one node per thread there (BF16 + rest + SR, us per step, one node per
+// thread against this: decay 200 x 150 x 100 57 and 48, 342 x 39 x 129 35 and 29, D3Q27 56 and
+// 41; porous 120^3 40 and 33, 400 x 200 x 60 128 and 96), 5 % slower on 186-node rows (73 % of the
+// lanes), up to twice on rows of 34 and 50. Everywhere else one node per thread was faster or
+// within 5 %: FP32 and FP64 are bound by memory either way, and with velocities or a tensor field
+// the two-node kernels keep too few waves.
+template <class ST, int UM>
+static bool try_launch_ragged(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a_in) {
+    if constexpr (sizeof(ST) == 2 && UM == 0) {
+        constexpr int V = 2;
+        const int nx = h->cfg.nx, waves = (nx + 64 * V - 1) / (64 * V);
+        if (!(a_in.rest32 || a_in.sround) || h->t_field_mode == 1 || nx % V != 0 || waves > 8 || 4 * nx < 3 * 64 * V * waves)
+            return false;
+        StepArgs<typename Store<ST>::Real> a = a_in;
+        a.waves = waves;
+        a.rows = waves >= 3 ? 1 : 4 / waves;
+        const dim3 block(64 * waves, a.rows, 1);
+        const dim3 grid(1, (h->cfg.ny + a.rows - 1) / a.rows, h->cfg.nz);
+        if (a.abb) hipLaunchKernelGGL((k_step_vec<ST, UM, V, 0, true, true>), grid, block, 0, h->stream, a);
+        else hipLaunchKernelGGL((k_step_vec<ST, UM, V, 0, false, true>), grid, block, 0, h->stream, a);
+        return true;
+    }
+    return false;
 }
 
 template <class ST, int UM, int V>
@@ -703,7 +754,8 @@ static bool prefer_one_node(const elbm_lattice* h, int V, int W, bool rs) {
 
 // Row-vector launch if the row shape allows it: nx = 64 V W with 1 <= W <= 8;
 // (flags >> 4) & 0xF sets the width. Without an explicit width, preferred_width's choice, or
-// the nearest width (smaller first) that fits the row, unless prefer_one_node.
+// the nearest width (smaller first) that fits the row, unless prefer_one_node; rows that no
+// width fits may take the ragged form.
 template <class ST, int UM>
 static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a) {
     const int nx = h->cfg.nx;
@@ -717,7 +769,8 @@ static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<
             V = c;
             break;
         }
-        if (V == 0 || prefer_one_node<ST, UM>(h, V, nx / (64 * V), sizeof(ST) == 2 && (a.rest32 || a.sround)))
+        if (V == 0) return try_launch_ragged<ST, UM>(h, a);
+        if (prefer_one_node<ST, UM>(h, V, nx / (64 * V), sizeof(ST) == 2 && (a.rest32 || a.sround)))
             return false;
     }
     if (sizeof(ST) == 8 && V > 2) return false;
