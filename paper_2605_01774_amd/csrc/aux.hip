@@ -232,6 +232,7 @@ __device__ inline void put_node(const StepArgs<typename Store<ST>::Real>& a, ST*
 template <class ST, int MODE>
 __global__ void k_init(StepArgs<typename Store<ST>::Real> a, int umode, const double* phi0,
                        const double* j0) {
+    touch_args<StepArgs<typename Store<ST>::Real>>();
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     const double p = phi0[k];
@@ -382,6 +383,7 @@ __device__ inline void node_moments(const StepArgs<typename Store<ST>::Real>& a,
 
 template <class ST>
 __global__ void k_moments(StepArgs<typename Store<ST>::Real> a, int umode, double* phi, double* q3) {
+    touch_args<StepArgs<typename Store<ST>::Real>>();
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
     double dphi, q[3];
@@ -439,6 +441,7 @@ template <class ST>
 __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<ST>::Real> a, int umode,
                                                         double* part, unsigned long long* ticket, double add_mass,
                                                         double* out) {
+    touch_args<StepArgs<typename Store<ST>::Real>>();
     __shared__ double sh[kRedThreads / 64];
     __shared__ int last;
     double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0};
@@ -477,6 +480,7 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<
 template <class ST>
 __global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>::Real> a, int umode, double* part,
                                                      unsigned long long* ticket, double* out) {
+    touch_args<StepArgs<typename Store<ST>::Real>>();
     __shared__ double sh[kRedThreads / 64];
     __shared__ int last;
     double m = __builtin_huge_val();

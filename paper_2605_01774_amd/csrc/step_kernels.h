@@ -123,6 +123,7 @@ __global__ __launch_bounds__(512) void k_step(const StepArgs<typename Store<ST>:
     constexpr bool SU = storage_units<ST, RS, ROOT>();
     const Real su = SU ? a.inv_scale : Real(1);  // physical value -> storage units
     const int rest32 = RS ? a.rest32 : 0;
+    touch_args<StepArgs<Real>>();
     int x, y;
     if (!node_of<ROW>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
     const int z = blockIdx.z;
@@ -355,6 +356,7 @@ __global__ __launch_bounds__(W > 4 ? 64 * W : (W ? 256 : 512)) void k_step_vec(
     const StepArgs<typename Store<ST>::Real> a) {
     using Real = typename Store<ST>::Real;
     using IO = VecIO<ST, V>;
+    touch_args<StepArgs<Real>>();
     constexpr bool SU = storage_units<ST, RS, false>();
     const Real su = SU ? a.inv_scale : Real(1);  // physical value -> storage units
     constexpr bool RAG = W == 0;
@@ -787,6 +789,7 @@ static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<
 template <class ST, int UM, bool ABB>
 __global__ __launch_bounds__(256) void k_adjoint(const StepArgs<typename Store<ST>::Real> a) {
     using Real = typename Store<ST>::Real;
+    touch_args<StepArgs<Real>>();
     int x, y;
     if (!node_of<false>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
     const int z = blockIdx.z;
