@@ -856,7 +856,7 @@ static hipError_t step_t(const elbm_lattice* h, const void* src, void* dst, doub
     if (h->cfg.root_rho < 0 && !(h->cfg.flags & ELBM_FLAG_SCALAR_KERNEL) &&
         try_launch_vec<ST, UM>(h, a))
         return hipGetLastError();
-    const RowGrid rg = grid_for(h);
+    const RowGrid rg = grid_for(h, memory_paced<ST>(h));
     const dim3 grid = rg.grid, block = rg.block;
     a.rows = rg.rows;
     const bool root = h->cfg.root_rho >= 0, abb = a.abb != 0;
@@ -908,7 +908,7 @@ static hipError_t adj_t(const elbm_lattice* h, const void* state, double src_mul
     a.adj_in = static_cast<const Real*>(adj_in);
     a.adj_out = static_cast<Real*>(adj_out);
     a.t_grad = static_cast<Real*>(t_grad);
-    const RowGrid rg = grid_for(h, 256);  // gathers and local writes: rows may be split
+    const RowGrid rg = grid_for(h, false, 256);  // gathers and local writes: rows may be split
     const dim3 grid = rg.grid, block = rg.block;
     a.rows = rg.rows;
     if (a.abb)
