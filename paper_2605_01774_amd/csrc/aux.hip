@@ -692,13 +692,13 @@ hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part) {
+hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsigned long long* ticket) {
     const int nb = h->part_blocks;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
         hipLaunchKernelGGL(k_reduce<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, part,
-                           h->d_ticket, double(h->n) * h->cfg.phi_ref, out4);
+                           ticket, double(h->n) * h->cfg.phi_ref, out4);
     });
     return hipGetLastError();
 }

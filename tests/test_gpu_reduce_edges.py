@@ -41,3 +41,24 @@ def test_reduce_at_block_edges(shape, prec):
         lat.reduce_noalloc(dev)
         assert torch.equal(dev.cpu(), torch.from_numpy(got))
         assert lat.min_population() == float(lat.populations().min())
+
+
+def test_reduce_beside_noalloc_on_another_stream():
+    """The sums that the host waits for and those of reduce_noalloc count their blocks apart, so
+    one may run while the other is in flight on another stream."""
+    banner("reduction beside a reduction on another stream")
+    lat = lattice.Lattice(128, 128, 64, precision="f32", phi_ref=1.0, device="cuda:0")
+    lat.set_diffusion([2e-2, 1e-3, 0, 1e-2, 0, 5e-3])
+    gen = torch.Generator(device="cuda:0").manual_seed(5)
+    lat.init_equilibrium(1.0 + torch.rand(64, 128, 128, generator=gen, dtype=torch.float64, device="cuda:0"))
+    want = lat.reduce()
+    one, two = torch.cuda.Stream(), torch.cuda.Stream()
+    dev = torch.zeros(20, 4, dtype=torch.float64, device="cuda:0")
+    torch.cuda.synchronize()
+    for k in range(20):
+        lat.set_stream(one)
+        lat.reduce_noalloc(dev[k])
+        lat.set_stream(two)
+        assert (lat.reduce() == want).all()
+    torch.cuda.synchronize()
+    assert (dev.cpu().numpy() == want).all()
