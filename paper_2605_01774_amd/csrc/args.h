@@ -246,23 +246,27 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
 // fill the chip (31 x 119 x 238 FP16 + rest + SR: 36 us against 22.5), blocks beyond 256 threads
 // by the waves that fit a CU (200 x 150 x 100 FP64, rows in pairs: 169 us against 159).
 //
-// Packing trades idle threads for blocks that end later; where memory sets the pace idle threads
-// cost nothing, and rows longer than a wavefront stay alone. That is so in FP64 and FP32 with a
-// state beyond half of the 256 MB cache, FP64 with a velocity per node (bound by its arithmetic)
-// aside. Alone and packed, us per step: 90 x 200 x 150 FP64 with a constant velocity 183 and 194,
-// FP32 105 and 109, 90 x 300 x 300 FP32 322 and 330; against that 90 x 100 x 50 FP32 15.3 and
-// 14.8, 70 x 120 x 120 FP32 32.2 and 29.5, 90 x 200 x 150 FP64 with every field 227 and 218.
+// Where memory sets the pace (FP64 and FP32 with a state beyond half of the 256 MB cache; FP64
+// with a velocity per node is bound by its arithmetic) idle threads cost little, and blocks that
+// are not of two or four wavefronts lose. There rows longer than a wavefront stay alone, but for
+// four wavefronts: in FP32 those that leave fewer threads idle, in FP64 two rows. Alone, in three
+// and in four wavefronts, us per step with a constant velocity: FP32 90 x 200 x 150 105, 108, -;
+// 81 x 226 x 178 133, 136, 126; 78 x 189 x 185 110, 112, 107; FP64 90 x 200 x 150 184, 194, -;
+// 81 x 226 x 178 229, 238, 235; 118 x 200 x 200 340, -, 327; 105 x 200 x 200 300, -, 293. Below
+// that size packing wins as everywhere: 70 x 120 x 120 FP32 alone 32.2, packed 29.5; 90 x 100 x 50
+// 15.3 and 14.8; 90 x 200 x 150 FP64 with every field 227 and 218.
 struct RowGrid {
     dim3 grid, block;
     int rows;
 };
 template <class ST>
-inline bool memory_paced(const elbm_lattice* h) {
+inline int memory_paced(const elbm_lattice* h) {  // bytes of a stored value, 0 if it is not
     const double state = double(h->cfg.nx) * h->cfg.ny * h->cfg.nz * Q * sizeof(ST);
-    return sizeof(ST) >= 4 && !(sizeof(ST) == 8 && h->u_mode == 2) && h->cfg.root_rho < 0 &&
-           state > 128e6;
+    const bool paced = sizeof(ST) >= 4 && !(sizeof(ST) == 8 && h->u_mode == 2) &&
+                       h->cfg.root_rho < 0 && state > 128e6;
+    return paced ? int(sizeof(ST)) : 0;
 }
-inline RowGrid grid_for(const elbm_lattice* h, bool streams, int max_threads = 512) {
+inline RowGrid grid_for(const elbm_lattice* h, int paced, int max_threads = 512) {
     const int nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz;
     RowGrid g;
     if (nx > max_threads) {
@@ -277,7 +281,9 @@ inline RowGrid grid_for(const elbm_lattice* h, bool streams, int max_threads = 5
     for (int r = 1; r <= ny && (r == 1 || r * nx <= 256); ++r) {
         const int threads = (r * nx + 63) / 64 * 64, groups = (ny + r - 1) / r;
         const double use = double(nx) * ny / (double(threads) * groups);
-        if ((use > best_use * 1.05 && (r == 1 || !streams)) || best * nx <= 64) {
+        bool take = use > best_use * 1.05;
+        if (paced && nx > 64 && r > 1) take = threads == 256 && (paced == 8 ? r == 2 : take);
+        if (take || best * nx <= 64) {
             best = r;
             best_use = use;
         }

@@ -18,14 +18,16 @@
 // is that of the single-step kernels, so the state after the launch is bitwise that of two
 // single steps.
 //
-// What bounds it, measured on MI355X (256^3 decay, FP32): the cache lines that the loads and
-// stores touch, not HBM and not the collisions (150 us per step without memory accesses, 36
-// of that for the halo). Over all tilings an iteration of a full chip takes
-// 1.2 us + 0.075 us per line and run of a block (pair_plan), which is why whole rows and wide
-// tiles win although they recompute more. Per step, single steps against this kernel, same
-// box: decay 256^3 FP32 429 -> 306 us, FP64 893 -> 707; 384^3 FP32 1531 -> 1072, FP64 3516 ->
-// 1913; porous 384^3 (walls, material table) FP32 1543 -> 1181, FP64 3017 -> 2263;
-// 200 x 150 x 100 FP32 87 -> 63; 128^3 FP32 53 -> 42, FP64 105 -> 84; 96^3 FP32 21.9 -> 19.1.
+// What bounds it on MI355X: not HBM, the counters read 2-11 % over one pass per two steps at
+// 3.8-4.5 TB/s. Over all tilings an iteration of a full chip takes 1.2 us + 0.075 us per cache line
+// and run of a block (pair_plan), which is why whole rows and wide tiles win although they
+// recompute more. On the 256^3 decay in FP32, with tiles of two whole rows and as many halo rows,
+// VALU issue is as busy (1.02 of SIMD cycles, 623 instructions per node and step against 373 in a
+// single step; 150 us per step without memory accesses, 36 of that for the halo); elsewhere it is
+// at 0.31-0.61. Per step, single steps against this kernel, same box: decay 256^3 FP32 429 -> 306
+// us, FP64 893 -> 707; 384^3 FP32 1531 -> 1072, FP64 3516 -> 1913; porous 384^3 (walls, material
+// table) FP32 1543 -> 1181, FP64 3017 -> 2263; 200 x 150 x 100 FP32 87 -> 63; 128^3 FP32 53 -> 42,
+// FP64 105 -> 84; 96^3 FP32 21.9 -> 19.1.
 // Not taken elsewhere, where it measured slower: with a velocity (256^3 plume FP32 428 -> 500,
 // FP64 880 -> 945; 512^3 field FP64 8.6 -> 18.6 ms, spilled registers) and for the 16-bit
 // forms (decay 256^3 BF16 216 -> 280), whose single steps are bound by VALU issue or close to

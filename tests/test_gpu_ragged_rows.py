@@ -67,3 +67,24 @@ def test_ragged_rows_bitwise(q, form, kind, bc):
         assert got[1] == ref[1], nx
         for a, b in zip(got[2:], ref[2:]):
             assert torch.equal(a, b), nx
+
+
+@pytest.mark.parametrize("prec,nx,ny,nz", [("f64", 105, 95, 92), ("f64", 81, 105, 108), ("f64", 33, 161, 164),
+                                           ("f32", 81, 145, 148), ("f32", 105, 121, 140)])
+def test_rows_of_large_lattices(prec, nx, ny, nz):
+    """Rows are laid out over blocks by another rule beyond 128 MB of state: a lattice over that
+    size of two equal halves in z against one of half the size, bitwise."""
+    banner(f"rows of a large lattice {nx}x{ny}x{nz} {prec}")
+    per = 19 * (8 if prec == "f64" else 4)
+    assert nx * ny * nz * per > 128e6 > nx * ny * (nz // 2) * per
+    gen = torch.Generator(device="cuda:0").manual_seed(nx)
+    half = 1.0 + 0.2 * torch.rand(nz // 2, ny, nx, generator=gen, dtype=torch.float64, device="cuda:0")
+    out = []
+    for phi0 in (half, torch.cat([half, half])):
+        lat = lattice.Lattice(nx, ny, phi0.shape[0], precision=prec, phi_ref=1.0, device="cuda:0")
+        lat.set_diffusion([1e-2, 2e-3, -1e-3, 8e-3, 1e-3, 5e-3])
+        lat.set_velocity([0.04, -0.02, 0.03])
+        lat.init_equilibrium(phi0)
+        lat.step(3)
+        out.append(lat.populations())
+    assert torch.equal(out[1], torch.cat([out[0], out[0]], dim=1))
