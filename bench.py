@@ -9,7 +9,8 @@ deviations, as BF16 / FP16 deviations (round to nearest even), and as BF16 / FP1
 FP32 rest population and stochastic rounding ("bf16r", "fp16r"). Every variant's error is
 taken after --err-steps steps (200) against the FP64 GPU run of the same input and step
 count, in a run of its own after the timing. A step is one launch of the step kernel over
-all 512^3 nodes. The headline runs exactly --warmup and --steps steps; the variants and
+all 512^3 nodes (on the u = 0 sub-workloads the FP64 and FP32 forms take two steps per launch:
+their achieved_gbs counts the bytes of a launch once, half of bytes_per_lup per step). The headline runs exactly --warmup and --steps steps; the variants and
 sub-workloads warm up and are timed for at least --min-ms (150 ms) of GPU time each, since
 kernels of a few hundred microseconds run slower for the first tens of milliseconds.
 
@@ -48,7 +49,7 @@ HBM_PEAK_GBS = 8000.0
 Q = 19  # velocity set of the run (--q 27 times the D3Q27 build)
 
 
-KERNEL_SOURCES = ["step_kernels.h", "node.h", "lattice.h", "args.h", "fmath.h"]
+KERNEL_SOURCES = ["step_kernels.h", "pair_kernel.h", "node.h", "lattice.h", "args.h", "fmath.h"]
 
 
 def code_without_comments(text: str) -> str:
@@ -58,7 +59,7 @@ def code_without_comments(text: str) -> str:
 
 
 def kernel_source_hash() -> str:
-    """SHA-256 over the step kernel's sources with comments and blank space removed (tags
+    """SHA-256 over the step kernels' sources with comments and blank space removed (tags
     the traffic counters with the code they were taken from; editing a comment keeps it)."""
     import hashlib
     h = hashlib.sha256()
@@ -68,22 +69,32 @@ def kernel_source_hash() -> str:
     return h.hexdigest()
 
 
-def measured_traffic(precision: str, workload: str):
-    """HBM bytes per launch of the step kernel on this workload, from the committed
-    rocprofv3 counter summary (FETCH_SIZE and WRITE_SIZE, copy-calibrated), or None if the
-    summary is missing or was taken from different kernel sources."""
+def counter_summary(precision: str, workload: str) -> dict:
+    """The committed rocprofv3 counter summary of a workload's step kernel, empty if missing."""
     path = os.path.join(ROOT, "profiles", f"step_{precision}_{workload}_hbm_traffic.txt")
-    if not os.path.exists(path):
-        return None
     vals = {}
-    with open(path) as fh:
-        for line in fh:
-            if ":" in line and not line.startswith("#"):
-                k, v = line.split(":", 1)
-                vals[k.strip()] = v.strip()
+    if os.path.exists(path):
+        with open(path) as fh:
+            for line in fh:
+                if ":" in line and not line.startswith("#"):
+                    k, v = line.split(":", 1)
+                    vals[k.strip()] = v.strip()
+    return vals
+
+
+def steps_per_launch(precision: str, workload: str) -> int:
+    """Steps that one launch of the step kernel takes on this workload."""
+    return int(counter_summary(precision, workload).get("steps_per_launch", 1))
+
+
+def measured_traffic(precision: str, workload: str):
+    """HBM bytes per step on this workload, from the committed counter summary (FETCH_SIZE and
+    WRITE_SIZE, copy-calibrated; per launch over the steps it takes), or None if the summary is
+    missing or was taken from different kernel sources."""
+    vals = counter_summary(precision, workload)
     if vals.get("kernel_source_sha256") != kernel_source_hash():
         return None
-    return float(vals["traffic_bytes_per_launch"])
+    return float(vals["traffic_bytes_per_launch"]) / int(vals.get("steps_per_launch", 1))
 
 
 # Storage forms timed by the bench: the library's precision forms, plus the 16-bit forms
@@ -229,8 +240,9 @@ def run_workload(wl, steps, warmup, err_steps, forms, phases, log, headline=None
             r["err"], r["mass_err"] = None, None
         del phi
         b = bytes_per_lup(form, prob, phases)
-        ach = b * prob.n / (r["launch_ms"] * 1e-3) / 1e9
-        r.update(bytes_per_lup=b, achieved_gbs=ach, frac=ach / HBM_PEAK_GBS,
+        per = steps_per_launch(form, wl_tag_of(wl, phases))
+        ach = b / per * prob.n / (r["launch_ms"] * 1e-3) / 1e9
+        r.update(bytes_per_lup=b, steps_per_launch=per, achieved_gbs=ach, frac=ach / HBM_PEAK_GBS,
                  mlups=prob.n * r["steps"] / r["wall_s"] / 1e6)
         out[form] = r
     del ref
@@ -241,7 +253,8 @@ def run_workload(wl, steps, warmup, err_steps, forms, phases, log, headline=None
 def form_summary(r, form, wl_tag):
     s = dict(mlups=round(r["mlups"], 1), ms_per_step=round(r["launch_ms"], 4),
              steps=r["steps"], warmup=r["warmup"],
-             bytes_per_lup=r["bytes_per_lup"], achieved_gbs=round(r["achieved_gbs"], 1),
+             bytes_per_lup=r["bytes_per_lup"], steps_per_launch=r["steps_per_launch"],
+             achieved_gbs=round(r["achieved_gbs"], 1),
              frac=round(r["frac"], 4), traffic=measured_traffic(form, wl_tag),
              max_err=r["err"], mass_err=r["mass_err"], fallback_node_updates=r["fallback"])
     if r["k_eff"] is not None:
