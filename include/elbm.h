@@ -6,11 +6,11 @@
  * library is built once per velocity set with this same ABI: libelbm.so (D3Q19) and
  * libelbm27.so (D3Q27, the paper's 3-D lattice, Sec. 2.1). Q below is 19 or 27.
  *
- * One time step = one HIP kernel: per node, the flux/ghost split of the non-equilibrium
- * populations (Sec. 2.2), the tensorial flux relaxation with S = (I/2 + D/cs^2)^-1
- * (Sec. 2.3), the ADE-corrected entropic ghost amplitude lambda (Sec. 2.5, App. B), the
- * positivity fallback alpha (Sec. 2.6), then streaming (Sec. 2.1). Sources use the midpoint
- * splitting of Sec. 3.3.
+ * One HIP kernel takes a whole time step (two of them in some runs, see elbm_step): per node,
+ * the flux/ghost split of the non-equilibrium populations (Sec. 2.2), the tensorial flux
+ * relaxation with S = (I/2 + D/cs^2)^-1 (Sec. 2.3), the ADE-corrected entropic ghost amplitude
+ * lambda (Sec. 2.5, App. B), the positivity fallback alpha (Sec. 2.6), then streaming
+ * (Sec. 2.1). Sources use the midpoint splitting of Sec. 3.3.
  *
  * Conventions
  *  - Grid nx * ny * nz, node index k = (z * ny + y) * nx + x (x fastest). Every per-node
@@ -145,8 +145,9 @@ int64_t elbm_field_plane_bytes(const elbm_lattice* h);
 
 /* Bind the two population buffers (device, at least elbm_population_bytes each, distinct,
  * not aliased, 16-byte aligned: the step kernels access up to 16 bytes per lane). Step
- * kernels read one and write the other, then swap. EINVAL for null, equal or misaligned
- * buffers, ESHAPE for short ones. */
+ * kernels read one and write the other; buf_a holds the first state, and after each call that
+ * steps the state is in the buffer that one swap per step leads to. EINVAL for null, equal or
+ * misaligned buffers, ESHAPE for short ones. */
 int elbm_bind_populations(elbm_lattice* h, void* buf_a, int64_t buf_a_bytes, void* buf_b,
                           int64_t buf_b_bytes);
 
@@ -219,7 +220,11 @@ int elbm_set_dirichlet(elbm_lattice* h, double phi_lo, double phi_hi);
 int elbm_init_equilibrium(elbm_lattice* h, const double* phi0, int64_t phi0_bytes, const double* j0,
                           int64_t j0_bytes);
 
-/* Advance n_steps >= 0 time steps (one kernel launch each, asynchronous). */
+/* Advance n_steps >= 0 time steps, asynchronously: one kernel launch each, or, in FP64 and FP32
+ * at zero velocity (D3Q19) where that is faster, one per two steps for the first 4 (n_steps / 4)
+ * of them. Either way the state ends in the buffer that n_steps swaps lead to, so a call of an
+ * even number of steps may be captured in a HIP graph and replayed (after a first call where a
+ * source is set: the first step of a run takes half a source step less than the following). */
 int elbm_step(elbm_lattice* h, int64_t n_steps);
 
 /* As elbm_step, and record per node and step the amplitude lambda used (device, working

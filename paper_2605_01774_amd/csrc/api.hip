@@ -589,9 +589,13 @@ static int do_steps(elbm_lattice* h, int64_t n_steps, void* lam_rec, uint8_t* br
     if (!h->t_set) return fail(ELBM_ESTATE, "diffusion tensor not set");
     if (int r = set_device(h)) return r;
     const int rb = real_bytes(h->cfg.precision);
+    // A launch of two steps swaps the buffers once, two single steps swap them twice. An even
+    // number of such launches per call leaves the state in the buffer where single steps would:
+    // a captured call of an even number of steps reads on replay what it wrote before.
+    const int64_t paired = n_steps / 4 * 4;
     bool pairs = true;
     for (int64_t s = 0; s < n_steps; ++s) {
-        if (pairs && s + 2 <= n_steps) {
+        if (pairs && s < paired) {
             void* lam[2];
             uint8_t* br[2];
             for (int m = 0; m < 2; ++m) {
