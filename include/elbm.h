@@ -260,7 +260,8 @@ int elbm_reduce(elbm_lattice* h, double* out4);
  * device array of 64 KiB per GPU (enough for the 2048 first-pass blocks the library ever
  * uses; ESHAPE otherwise), which every call on that GPU shares and overwrites completely.
  * Calls that overlap on one GPU (other threads, other streams) race on that array.
- * Like a captured step, a captured call uses the handle's memory: the handle has to outlive it.
+ * It uses no memory of the handle: a captured call may be replayed after elbm_destroy, as long as
+ * out4, the bound buffers and the field stores live.
  * Errors: EINVAL (null handle or out4), ESHAPE (out4 too small, or buffers not bound),
  * ESTATE (not initialised, no tensor). */
 int elbm_reduce_noalloc(elbm_lattice* h, double* out4, int64_t out4_bytes);

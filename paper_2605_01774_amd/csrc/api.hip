@@ -330,7 +330,7 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     h->part_blocks = int(nb < kMaxPartBlocks ? nb : kMaxPartBlocks);
     if (h->part_blocks < 1) h->part_blocks = 1;
     const size_t bytes = sizeof(double) * 4 * (size_t)h->part_blocks + kCntWords * sizeof(unsigned long long) +
-                         sizeof(long long) + 2 * sizeof(unsigned long long);
+                         sizeof(long long) + sizeof(unsigned long long);
     void* scratch = nullptr;
     e = hipMalloc(&scratch, bytes);
     if (e != hipSuccess) {
@@ -341,8 +341,8 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     h->d_cnt = reinterpret_cast<unsigned long long*>(h->d_part + 4 * h->part_blocks);
     h->d_flag = reinterpret_cast<long long*>(h->d_cnt + kCntWords);
     h->d_ticket = reinterpret_cast<unsigned long long*>(h->d_flag + 1);
-    // counters, flag and tickets start at zero
-    e = hipMemset(h->d_cnt, 0, (kCntWords + 3) * sizeof(unsigned long long));
+    // counters, flag and ticket start at zero
+    e = hipMemset(h->d_cnt, 0, (kCntWords + 2) * sizeof(unsigned long long));
     if (e != hipSuccess) {
         (void)hipFree(scratch);
         delete h;
@@ -688,7 +688,7 @@ int elbm_reduce_noalloc(elbm_lattice* h, double* out4, int64_t out4_bytes) {
     if (int r = set_device(h)) return r;
     double* part = static_cast<double*>(scratch_of(h->device));
     if (!part) return fail(ELBM_ESTATE, "static scratch not resolved on this device");
-    HIP_OK(launch_reduce(h, out4, part, h->d_ticket + 1), "reduce (static scratch)");
+    HIP_OK(launch_reduce(h, out4, part, nullptr), "reduce (static scratch)");
     return ELBM_OK;
 }
 

@@ -397,8 +397,10 @@ __global__ void k_moments(StepArgs<typename Store<ST>::Real> a, int umode, doubl
 }
 
 // Global sums: Neumaier-compensated accumulation per thread (grid-stride), then an FP64 sum over
-// the block, and the sum over the blocks by the block that finishes last, in the same launch.
-// A second launch of one block took 3.8 us after a first of 10.4 at 32^3.
+// the block, and the sum over the blocks: by the block that finishes last, in the same launch,
+// where the handle counts its blocks (synchronous calls: no two launches of a handle overlap, and
+// the handle outlives them), and by a second launch of one block otherwise, in the same order. That
+// second launch took 3.8 us after a first of 10.4 at 32^3.
 constexpr int kRedThreads = 256;
 
 __device__ inline void neumaier(double& sum, double& comp, double v) {
@@ -437,6 +439,22 @@ __device__ inline bool last_block(unsigned long long* ticket, int* flag) {
     return *flag != 0;
 }
 
+// Sum of the nb block partials, by one block: each thread takes a strided subset of them.
+__device__ inline void sum_partials(const double* part, int nb, double add_mass, double* out, double* sh) {
+    double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0}, r[4];
+    for (int b = threadIdx.x; b < nb; b += kRedThreads)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], part[4 * b + m]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
+    if (threadIdx.x == 0) {
+        out[0] = add_mass + r[0];
+#pragma unroll
+        for (int m = 1; m < 4; ++m) out[m] = r[m];
+    }
+}
+
+// ticket null: the partials only
 template <class ST>
 __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<ST>::Real> a, int umode,
                                                         double* part, unsigned long long* ticket, double add_mass,
@@ -459,20 +477,14 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<
 #pragma unroll
         for (int m = 0; m < 4; ++m) part[4 * blockIdx.x + m] = r[m];
     }
-    if (!last_block(ticket, &last)) return;
-    // each thread takes a strided subset of the block partials
-#pragma unroll
-    for (int m = 0; m < 4; ++m) sum[m] = comp[m] = 0.0;
-    for (int b = threadIdx.x; b < int(gridDim.x); b += kRedThreads)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], part[4 * b + m]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
-    if (threadIdx.x == 0) {
-        out[0] = add_mass + r[0];
-#pragma unroll
-        for (int m = 1; m < 4; ++m) out[m] = r[m];
-    }
+    if (!ticket || !last_block(ticket, &last)) return;
+    sum_partials(part, int(gridDim.x), add_mass, out, sh);
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_reduce_final(const double* part, int nb, double add_mass,
+                                                              double* out) {
+    __shared__ double sh[kRedThreads / 64];
+    sum_partials(part, nb, add_mass, out, sh);
 }
 
 // Smallest current population g_i (full value, as the population readout gives it, with
@@ -694,12 +706,14 @@ hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3) {
 
 hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsigned long long* ticket) {
     const int nb = h->part_blocks;
+    const double mass = double(h->n) * h->cfg.phi_ref;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
         hipLaunchKernelGGL(k_reduce<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, part,
-                           ticket, double(h->n) * h->cfg.phi_ref, out4);
+                           ticket, mass, out4);
     });
+    if (!ticket) hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedThreads), 0, h->stream, part, nb, mass, out4);
     return hipGetLastError();
 }
 
