@@ -341,7 +341,9 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     h->d_cnt = reinterpret_cast<unsigned long long*>(h->d_part + 4 * h->part_blocks);
     h->d_flag = reinterpret_cast<long long*>(h->d_cnt + kCntWords);
     h->d_ticket = reinterpret_cast<unsigned long long*>(h->d_flag + 1);
-    // counters, flag and ticket start at zero
+    // counters, flag and ticket start at zero (4.5 us for a size that 16 bytes do not divide, 2.6 us
+    // for this one)
+    static_assert((kCntWords + 2) * sizeof(unsigned long long) % 16 == 0, "whole 16-byte words");
     e = hipMemset(h->d_cnt, 0, (kCntWords + 2) * sizeof(unsigned long long));
     if (e != hipSuccess) {
         (void)hipFree(scratch);
