@@ -35,7 +35,8 @@ struct StepArgs {
     int xcd_remap;  // row-vector kernel: XCD slab block order (xcd_block)
     int rows;       // one-node-per-thread kernels, ragged row-vector: x-rows of a block
     int waves;      // row-vector kernel on ragged rows: wavefronts of a row
-    float inv_nx;   // 1 / nx, for blocks of several rows
+    int pitch;      // threads of a row in blocks of several rows, and 1 / pitch
+    float inv_pitch;
     Real* lam_rec;
     uint8_t* br_rec;
     unsigned long long* counters;
@@ -225,7 +226,8 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
     a.xcd_remap = 0;
     a.rows = 1;
     a.waves = 1;
-    a.inv_nx = 1.0f / float(h->cfg.nx);
+    a.pitch = h->cfg.nx;
+    a.inv_pitch = 1.0f;
     a.phi_lo = Real(h->phi_lo);
     a.phi_hi = Real(h->phi_hi);
     a.counters = h->d_cnt;
@@ -233,84 +235,120 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
 }
 
 // Launch shape of the one-node-per-thread kernels: a block takes `rows` whole x-rows, its
-// threads numbered through them (node_of), so that the x-shifted pushes stay inside the
-// block's own cache lines and no line is written by two blocks (which may sit on different
-// XCDs with separate L2s). Rows longer than max_threads are cut into segments of max_threads.
+// threads numbered through them `pitch` per row (node_of), so that the x-shifted pushes stay
+// inside the block's own cache lines and no line is written by two blocks (which may sit on
+// different XCDs with separate L2s). Rows longer than max_threads are cut into segments of it.
 //
-// Short rows are packed until the fewest threads are idle, in the smallest such block of 128
-// to 256 threads (a few per cent of idle threads aside). One row per 32 or 64 threads, stacked
-// to 256, left half the lanes of a 37- or 65-node row idle and put a 32^3 lattice on half of
-// the CUs. Before and after, us per step: 32^3 FP64 6.6 -> 5.4, FP32 4.6 -> 3.7, FP16 with rest
-// and SR 5.1 -> 4.2; 41 x 120 x 80 FP32 14.3 -> 12.5, FP16 + rest + SR 17.0 -> 13.0;
-// 65 x 50 x 70 FP64 with every field 29.1 -> 24.3. Blocks of one wavefront lose on lattices that
-// fill the chip (31 x 119 x 238 FP16 + rest + SR: 36 us against 22.5), blocks beyond 256 threads
-// by the waves that fit a CU (200 x 150 x 100 FP64, rows in pairs: 169 us against 159).
+// Padded: a row takes 32 or whole times 64 threads, rows are stacked to 256. Packed: as many
+// rows as 256 threads hold, without gaps. Rows over 128 nodes stay alone either way. Packing
+// leaves fewer threads idle, but a wavefront then covers parts of several rows and a block more
+// nodes. Which is faster was measured on rows of 8 to 128 nodes (about 60 lengths), 1e3 to 6e6
+// nodes, five kinds of coefficients and four forms; packed where
+//  - it takes a fifth fewer threads, in blocks of four wavefronts: 33 x 67 x 68 FP64 1.23 times
+//    as fast, 65- to 85-node rows 1.06-1.2 in every form, 1.25-1.39 with FP32 rest and SR; padded
+//    is faster on 28- to 31- and 55- to 64-node rows (by 1-13 %), and by 5-10 % where two rows
+//    make three wavefronts (86- to 96-node rows) but for the rounding forms on many blocks
+//    (packed 1.13);
+//  - the CU with the most blocks then has no more than 1 / 0.9 times the rows, 1 / 0.85 where
+//    arithmetic bounds the kernel (blocks go round the CUs: where 270 packed blocks take two rounds
+//    as 400 padded ones did, 0.76-0.9 times as fast without this condition);
+//  - rows are not of 17 to 31 nodes (padded to 32, two per wavefront; FP32 and plain BF16 0.7-1.05
+//    packed) and memory does not set the pace (state and coefficients beyond half of the 256 MB cache:
+//    FP32 0.9-1.05, FP64 0.93-1.05, plain BF16 0.89-1.1), unless arithmetic bounds the kernel: FP32 rest or SR,
+//    FP64 with a velocity per node (1.03-1.34 there), the exact root, the adjoint (1.02-1.3). Of 17
+//    to 31 nodes those to 21 then (1.04-1.3; 23 x 511 x 511 BF16 with FP32 rest and SR 0.91).
+// Over all of these sizes, against padded alone: FP64 1.03, FP32 1.02, BF16 1.04, BF16 with FP32
+// rest and SR 1.07, none below 0.94.
 //
-// Where memory sets the pace (FP64 and FP32 with a state beyond half of the 256 MB cache; FP64
-// with a velocity per node is bound by its arithmetic) idle threads cost little, and blocks that
-// are not of two or four wavefronts lose. There rows longer than a wavefront stay alone, but for
-// four wavefronts: in FP32 those that leave fewer threads idle, in FP64 two rows. Alone, in three
-// and in four wavefronts, us per step with a constant velocity: FP32 90 x 200 x 150 105, 108, -;
-// 81 x 226 x 178 133, 136, 126; 78 x 189 x 185 110, 112, 107; FP64 90 x 200 x 150 184, 194, -;
-// 81 x 226 x 178 229, 238, 235; 118 x 200 x 200 340, -, 327; 105 x 200 x 200 300, -, 293. Below
-// that size packing wins as everywhere: 70 x 120 x 120 FP32 alone 32.2, packed 29.5; 90 x 100 x 50
-// 15.3 and 14.8; 90 x 200 x 150 FP64 with every field 227 and 218.
-struct RowGrid {
-    dim3 grid, block;
-    int rows;
+// A lattice that 256-thread blocks would put on a part of the CUs takes the smallest packed blocks
+// that still find a CU each, if they have fewer wavefronts: 32^3 FP64 6.6 -> 5.4 us, FP32
+// 4.6 -> 3.7, FP16 with FP32 rest and SR 5.1 -> 4.2 in 256 blocks of 128 threads.
+struct RowRule {
+    bool arith;     // arithmetic bounds the kernel
+    bool rounding;  // 16-bit form with FP32 rest or stochastic rounding
+    bool paced;     // memory does
 };
 template <class ST>
-inline int memory_paced(const elbm_lattice* h) {  // bytes of a stored value, 0 if it is not
-    const double state = double(h->cfg.nx) * h->cfg.ny * h->cfg.nz * Q * sizeof(ST);
-    const bool paced = sizeof(ST) >= 4 && !(sizeof(ST) == 8 && h->u_mode == 2) &&
-                       h->cfg.root_rho < 0 && state > 128e6;
-    return paced ? int(sizeof(ST)) : 0;
+inline RowRule row_rule(const elbm_lattice* h) {
+    RowRule r;
+    r.rounding = sizeof(ST) == 2 && (h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING));
+    r.arith = r.rounding || (sizeof(ST) == 8 && h->u_mode == 2) || h->cfg.root_rho >= 0;
+    const int coefs = (h->t_field_mode == 1 ? 6 : 0) + (h->u_mode == 2 ? 3 : 0) + (h->r_mode == 2 ? 1 : 0);
+    r.paced = !r.arith && double(h->n) * (Q * sizeof(ST) + coefs * sizeof(typename Store<ST>::Real)) > 128e6;
+    return r;
 }
-inline RowGrid grid_for(const elbm_lattice* h, int paced, int max_threads = 512) {
+
+struct RowGrid {
+    dim3 grid, block;
+    int rows, pitch;
+
+    template <class Args>
+    void place(Args& a) const {
+        a.rows = rows;
+        a.pitch = pitch;
+        a.inv_pitch = 1.0f / float(pitch);
+    }
+};
+inline RowGrid grid_for(const elbm_lattice* h, const RowRule& rule, int max_threads = 512) {
     const int nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz;
     RowGrid g;
+    g.rows = 1;
     if (nx > max_threads) {
-        g.rows = 1;
+        g.pitch = nx;
         g.block = dim3(max_threads);
         g.grid = dim3((nx + max_threads - 1) / max_threads, ny, nz);
         return g;
     }
-    // the rows that leave the fewest threads idle
-    int best = 1;
-    double best_use = 0.0;
-    for (int r = 1; r <= ny && (r == 1 || r * nx <= 256); ++r) {
-        const int threads = (r * nx + 63) / 64 * 64, groups = (ny + r - 1) / r;
-        const double use = double(nx) * ny / (double(threads) * groups);
-        bool take = use > best_use * 1.05;
-        if (paced && nx > 64 && r > 1) take = threads == 256 && (paced == 8 ? r == 2 : take);
-        if (take || best * nx <= 64) {
-            best = r;
-            best_use = use;
+    const auto waves = [](int threads) { return (threads + 63) / 64; };
+    const auto blocks = [&](int rows) { return (long long)((ny + rows - 1) / rows) * nz; };
+    const auto rounds = [&](int rows) { return (blocks(rows) + h->cus - 1) / h->cus; };
+    g.pitch = nx <= 32 ? 32 : 64 * waves(nx);
+    if (nx <= 128) {
+        const int pad = min(256 / g.pitch, ny), most = min(256 / nx, ny);  // rows padded, packed
+        const int pad_waves = waves(pad * g.pitch);
+        g.rows = pad;
+        int packed = 0;
+        if (blocks(most) <= h->cus) {
+            const int top = blocks(pad) <= h->cus ? pad : most;
+            int r = 1;
+            while (r < top && blocks(r) > h->cus) ++r;
+            if (waves(r * nx) < pad_waves) packed = r;
+        } else {
+            const bool fewer = double(pad_waves) * double(blocks(pad)) >= 1.2 * waves(most * nx) * double(blocks(most));
+            const bool even = double(rounds(pad) * pad) >= (rule.arith ? 0.85 : 0.9) * double(rounds(most) * most);
+            const bool many = rule.rounding && blocks(pad) >= 8 * h->cus;
+            const bool halved = nx > 16 && nx < 32;  // padded to two rows per wavefront
+            if (fewer && even && (waves(most * nx) == 4 || many) && !rule.paced && (!halved || (rule.arith && nx <= 21)))
+                packed = most;
+            else if (many && nx > 64)
+                packed = 1;  // alone, its row in scalar registers (step_t): 1.03-1.08 times padded pairs
+        }
+        if (packed) {
+            g.rows = packed;
+            g.pitch = nx;
         }
     }
-    if ((ny + best - 1) / best > 65535) best = nx <= 256 ? 256 / nx : 1;  // grid size in y
-    g.rows = best;
-    g.block = dim3((best * nx + 63) / 64 * 64);
-    g.grid = dim3(1, (ny + best - 1) / best, nz);
+    g.block = dim3(64 * waves(g.rows * g.pitch));
+    g.grid = dim3(1, (ny + g.rows - 1) / g.rows, nz);
     return g;
 }
 
 // Node of a thread of a RowGrid launch; false if it has none. The row of thread t of a block of
-// several rows comes from a product with 1 / nx (exact: t < 512 keeps (t + 1/2) / nx further
+// several rows comes from a product with 1 / pitch (exact: t < 512 keeps (t + 1/2) / pitch further
 // from whole numbers than the product's rounding). ROW: one row per block, so that y is the same
 // for the block and stays in a scalar register, with every row address derived from it.
-template <bool ROW>
-__device__ __forceinline__ bool node_of(int nx, int ny, int rows, float inv_nx, int& x, int& y) {
+template <bool ROW, class Args>
+__device__ __forceinline__ bool node_of(const Args& a, int& x, int& y) {
     const int t = blockIdx.x * blockDim.x + threadIdx.x;
     if constexpr (ROW) {
         x = t;
         y = blockIdx.y;
-        return x < nx;
+        return x < a.nx;
     } else {
-        const int q = rows == 1 ? 0 : int((float(t) + 0.5f) * inv_nx);
-        x = t - q * nx;
-        y = blockIdx.y * rows + q;
-        return x < nx && q < rows && y < ny;
+        const int q = a.rows == 1 ? 0 : int((float(t) + 0.5f) * a.inv_pitch);
+        x = t - q * a.pitch;
+        y = blockIdx.y * a.rows + q;
+        return x < a.nx && q < a.rows && y < a.ny;
     }
 }
 

@@ -125,7 +125,7 @@ __global__ __launch_bounds__(512) void k_step(const StepArgs<typename Store<ST>:
     const int rest32 = RS ? a.rest32 : 0;
     touch_args<StepArgs<Real>>();
     int x, y;
-    if (!node_of<ROW>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
+    if (!node_of<ROW>(a, x, y)) return;
     const int z = blockIdx.z;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int nxy = nx * ny;
@@ -791,7 +791,7 @@ __global__ __launch_bounds__(256) void k_adjoint(const StepArgs<typename Store<S
     using Real = typename Store<ST>::Real;
     touch_args<StepArgs<Real>>();
     int x, y;
-    if (!node_of<false>(a.nx, a.ny, a.rows, a.inv_nx, x, y)) return;
+    if (!node_of<false>(a, x, y)) return;
     const int z = blockIdx.z;
     const int nx = a.nx, ny = a.ny, nz = a.nz;
     const int nxy = nx * ny;
@@ -856,9 +856,9 @@ static hipError_t step_t(const elbm_lattice* h, const void* src, void* dst, doub
     if (h->cfg.root_rho < 0 && !(h->cfg.flags & ELBM_FLAG_SCALAR_KERNEL) &&
         try_launch_vec<ST, UM>(h, a))
         return hipGetLastError();
-    const RowGrid rg = grid_for(h, memory_paced<ST>(h));
+    const RowGrid rg = grid_for(h, row_rule<ST>(h));
     const dim3 grid = rg.grid, block = rg.block;
-    a.rows = rg.rows;
+    rg.place(a);
     const bool root = h->cfg.root_rho >= 0, abb = a.abb != 0;
     const bool rs = sizeof(ST) == 2 && (a.rest32 || a.sround);
     const auto go = [&](auto row, auto rounding) {
@@ -908,9 +908,9 @@ static hipError_t adj_t(const elbm_lattice* h, const void* state, double src_mul
     a.adj_in = static_cast<const Real*>(adj_in);
     a.adj_out = static_cast<Real*>(adj_out);
     a.t_grad = static_cast<Real*>(t_grad);
-    const RowGrid rg = grid_for(h, 0, 256);  // gathers and local writes: rows may be split
+    const RowGrid rg = grid_for(h, {true, false, false}, 256);  // gathers and local writes: rows may be split
     const dim3 grid = rg.grid, block = rg.block;
-    a.rows = rg.rows;
+    rg.place(a);
     if (a.abb)
         hipLaunchKernelGGL((k_adjoint<ST, UM, true>), grid, block, 0, h->stream, a);
     else

@@ -1,0 +1,52 @@
+// Host program around the library's launch rules: reads one lattice per line of standard input and
+// prints the launch shape that the rules choose for it, without a GPU (256 compute units).
+//   rows <f64|f32|b16> <flags> <u_mode> <root> <nx> <ny> <nz>  ->  rows pitch threads grid.x grid.y grid.z covered
+// "covered" is 1 if every node of a plane has exactly one thread, by the arithmetic of node_of.
+#include <cstdio>
+#include <cstring>
+#include <vector>
+
+#include "step_kernels.h"
+
+using namespace elbm;
+
+static bool covered(const RowGrid& g, int nx, int ny) {
+    std::vector<int> seen(size_t(nx) * ny, 0);
+    const float inv_pitch = 1.0f / float(g.pitch);
+    for (unsigned by = 0; by < g.grid.y; ++by)
+        for (unsigned bx = 0; bx < g.grid.x; ++bx)
+            for (unsigned th = 0; th < g.block.x; ++th) {
+                const int t = int(bx * g.block.x + th);
+                const int q = g.rows == 1 ? 0 : int((float(t) + 0.5f) * inv_pitch);
+                const int x = t - q * g.pitch, y = int(by) * g.rows + q;
+                if (x < nx && q < g.rows && y < ny) {
+                    if (x < 0) return false;
+                    ++seen[size_t(y) * nx + x];
+                }
+            }
+    for (int s : seen)
+        if (s != 1) return false;
+    return true;
+}
+
+int main() {
+    char what[16], form[16];
+    int flags, u_mode, root, nx, ny, nz;
+    while (scanf("%15s %15s %d %d %d %d %d %d", what, form, &flags, &u_mode, &root, &nx, &ny, &nz) == 8) {
+        elbm_lattice h{};
+        h.cfg.nx = nx;
+        h.cfg.ny = ny;
+        h.cfg.nz = nz;
+        h.cfg.flags = flags;
+        h.cfg.root_rho = root ? 0.0 : -1.0;
+        h.n = int64_t(nx) * ny * nz;
+        h.u_mode = u_mode;
+        h.cus = 256;
+        const RowRule rule = !strcmp(form, "f64") ? row_rule<double>(&h)
+                             : !strcmp(form, "f32") ? row_rule<float>(&h) : row_rule<_Float16>(&h);
+        const RowGrid g = grid_for(&h, rule);
+        printf("%d %d %u %u %u %u %d\n", g.rows, g.pitch, g.block.x, g.grid.x, g.grid.y, g.grid.z,
+               int(covered(g, nx, ny)));
+    }
+    return 0;
+}
