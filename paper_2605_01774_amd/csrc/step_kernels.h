@@ -661,31 +661,38 @@ static void launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>:
     }
 }
 
-// Rows that no width divides: the 16-bit forms with FP32 rest or stochastic rounding at u = 0,
-// two nodes per lane, up to 1024 nodes, where at least three quarters of the lanes have nodes:
-// 4-37 % faster than one node per thread there (BF16 + rest + SR, us per step, one node per
-// thread against this: decay 200 x 150 x 100 57 and 48, 342 x 39 x 129 35 and 29, D3Q27 56 and
-// 41; porous 120^3 40 and 33, 400 x 200 x 60 128 and 96), 5 % slower on 186-node rows (73 % of the
-// lanes), up to twice on rows of 34 and 50. Everywhere else one node per thread was faster or
-// within 5 %: FP32 and FP64 are bound by memory either way, and with velocities or a tensor field
-// the two-node kernels keep too few waves.
+// Rows that no width divides: the 16-bit forms with FP32 rest or stochastic rounding at u = 0, two
+// nodes per lane, up to 1024 nodes, where more than three quarters of the lanes have nodes. BF16 +
+// rest + SR, us per step, one node per thread against this: decay 200 x 150 x 100 57 and 48, D3Q27
+// 56 and 41; porous 120^3 40 and 33, 400 x 200 x 60 128 and 96. Half the wavefronts of one node per
+// thread, so it needs lattices that fill the chip with them: from six per SIMD 1.02-1.3 times as
+// fast in rows of one to four wavefronts (rows of 100 to 510 nodes, both velocity sets), below that
+// 0.7-1.0 (200 x 27 x 28 8.1 us against 7.4); rows of five to eight wavefronts 1.0-1.2 from twenty
+// per SIMD in D3Q19, 0.8-0.9 in D3Q27 and on smaller lattices. Exactly three quarters of the lanes
+// (96 nodes) 0.92-1.04, 73 % (186) 0.95, rows of 34 and 50 half the speed. Everywhere else one node
+// per thread was faster or within 5 %: FP32 and FP64 are bound by memory either way, and with
+// velocities or a tensor field the two-node kernels keep too few waves.
+constexpr int kRaggedNodes = 2;  // nodes per lane
+// Wavefronts of a row in that form, 0 where it is not taken.
+inline int ragged_waves(const elbm_lattice* h) {
+    const int nx = h->cfg.nx, span = 64 * kRaggedNodes, waves = (nx + span - 1) / span;
+    if (!(h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING)) || h->u_mode != 0 ||
+        h->t_field_mode == 1 || nx % kRaggedNodes != 0 || waves > 8 || 4 * nx <= 3 * span * waves)
+        return 0;
+    const double per_simd = double(h->n / nx) * waves / (4.0 * h->cus);
+    if (waves <= 4) return per_simd >= 6.0 ? waves : 0;
+    return Q == 19 && per_simd >= 20.0 ? waves : 0;
+}
 template <class ST, int UM>
-static bool try_launch_ragged(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a_in) {
+static void launch_ragged(const elbm_lattice* h, StepArgs<typename Store<ST>::Real> a, int waves) {
     if constexpr (sizeof(ST) == 2 && UM == 0) {
-        constexpr int V = 2;
-        const int nx = h->cfg.nx, waves = (nx + 64 * V - 1) / (64 * V);
-        if (!(a_in.rest32 || a_in.sround) || h->t_field_mode == 1 || nx % V != 0 || waves > 8 || 4 * nx < 3 * 64 * V * waves)
-            return false;
-        StepArgs<typename Store<ST>::Real> a = a_in;
         a.waves = waves;
         a.rows = waves >= 3 ? 1 : 4 / waves;
         const dim3 block(64 * waves, a.rows, 1);
         const dim3 grid(1, (h->cfg.ny + a.rows - 1) / a.rows, h->cfg.nz);
-        if (a.abb) hipLaunchKernelGGL((k_step_vec<ST, UM, V, 0, true, true>), grid, block, 0, h->stream, a);
-        else hipLaunchKernelGGL((k_step_vec<ST, UM, V, 0, false, true>), grid, block, 0, h->stream, a);
-        return true;
+        if (a.abb) hipLaunchKernelGGL((k_step_vec<ST, UM, kRaggedNodes, 0, true, true>), grid, block, 0, h->stream, a);
+        else hipLaunchKernelGGL((k_step_vec<ST, UM, kRaggedNodes, 0, false, true>), grid, block, 0, h->stream, a);
     }
-    return false;
 }
 
 template <class ST, int UM, int V>
@@ -740,7 +747,8 @@ static int preferred_width(const elbm_lattice* h) {
     return tensor || (Q == 19 && nx > 320) ? 2 : 1;
 }
 template <class ST, int UM>
-static bool prefer_one_node(const elbm_lattice* h, int V, int W, bool rs) {
+static bool prefer_one_node(const elbm_lattice* h, int V, int W) {
+    const bool rs = h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING);
     const bool tnode = h->t_field_mode == 1, walls = h->cfg.bc_x == ELBM_DIRICHLET;
     if (sizeof(ST) == 8) {
         if (UM == 2) return Q == 27 && h->cfg.nx <= 256;
@@ -754,35 +762,44 @@ static bool prefer_one_node(const elbm_lattice* h, int V, int W, bool rs) {
     return W >= 5 && W <= 7 && (!rs || Q == 27);
 }
 
-// Row-vector launch if the row shape allows it: nx = 64 V W with 1 <= W <= 8;
-// (flags >> 4) & 0xF sets the width. Without an explicit width, preferred_width's choice, or
-// the nearest width (smaller first) that fits the row, unless prefer_one_node; rows that no
-// width fits may take the ragged form.
+// Row-vector kernel of a lattice: V nodes per lane and W wavefronts per row, nx = 64 V W with
+// W <= 8; W 0: the ragged form, of `waves`; V 0: the one-node-per-thread kernel. (flags >> 4) & 0xF
+// sets the width. Without an explicit width, preferred_width's choice, or the nearest width (smaller
+// first) that fits the row, unless prefer_one_node; rows that no width fits may take the ragged form.
+struct VecChoice {
+    int V = 0, W = 0, waves = 0;
+};
 template <class ST, int UM>
-static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a) {
-    const int nx = h->cfg.nx;
+static VecChoice choose_vec(const elbm_lattice* h) {
+    const int nx = h->cfg.nx, vmax = sizeof(ST) == 8 ? 2 : 4;
+    const auto fits = [&](int V) { return V >= 1 && V <= vmax && nx % (64 * V) == 0 && nx / (64 * V) <= 8; };
+    VecChoice c;
     int V = (h->cfg.flags >> ELBM_VECTOR_WIDTH_SHIFT) & 0xF;
     if (V == 0) {
         const int pref = preferred_width<ST, UM>(h);
-        const int vmax = sizeof(ST) == 8 ? 2 : 4;
         const int order[5] = {pref, pref / 2, pref / 4, pref * 2, pref * 4};
-        for (int c : order) {
-            if (c < 1 || c > vmax || nx % (64 * c) != 0 || nx / (64 * c) > 8) continue;
-            V = c;
-            break;
+        for (int m = 4; m >= 0; --m)
+            if (fits(order[m])) V = order[m];
+        if (V == 0) {
+            c.waves = sizeof(ST) == 2 ? ragged_waves(h) : 0;
+            c.V = c.waves ? kRaggedNodes : 0;
+            return c;
         }
-        if (V == 0) return try_launch_ragged<ST, UM>(h, a);
-        if (prefer_one_node<ST, UM>(h, V, nx / (64 * V), sizeof(ST) == 2 && (a.rest32 || a.sround)))
-            return false;
+        if (prefer_one_node<ST, UM>(h, V, nx / (64 * V))) return c;
     }
-    if (sizeof(ST) == 8 && V > 2) return false;
-    if (V != 1 && V != 2 && V != 4) return false;
-    if (nx % (64 * V) != 0) return false;
-    const int W = nx / (64 * V);
-    if (W < 1 || W > 8) return false;
-    if (V == 1) launch_vec_w<ST, UM, 1>(h, a, W);
-    else if (V == 2) launch_vec_w<ST, UM, 2>(h, a, W);
-    else if constexpr (sizeof(ST) != 8) launch_vec_w<ST, UM, 4>(h, a, W);
+    if (!fits(V)) return c;
+    c.V = V;
+    c.W = nx / (64 * V);
+    return c;
+}
+template <class ST, int UM>
+static bool try_launch_vec(const elbm_lattice* h, const StepArgs<typename Store<ST>::Real>& a) {
+    const VecChoice c = choose_vec<ST, UM>(h);
+    if (c.V == 0) return false;
+    if (c.W == 0) launch_ragged<ST, UM>(h, a, c.waves);
+    else if (c.V == 1) launch_vec_w<ST, UM, 1>(h, a, c.W);
+    else if (c.V == 2) launch_vec_w<ST, UM, 2>(h, a, c.W);
+    else if constexpr (sizeof(ST) != 8) launch_vec_w<ST, UM, 4>(h, a, c.W);
     return true;
 }
 

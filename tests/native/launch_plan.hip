@@ -1,6 +1,7 @@
 // Host program around the library's launch rules: reads one lattice per line of standard input and
 // prints the launch shape that the rules choose for it, without a GPU (256 compute units).
 //   rows <f64|f32|b16> <flags> <u_mode> <root> <nx> <ny> <nz>  ->  rows pitch threads grid.x grid.y grid.z covered
+//   vec <f64|f32|b16> <flags> <u_mode> <t_mode> <nx> <ny> <nz>  ->  V W waves of the row-vector kernel
 // "covered" is 1 if every node of a plane has exactly one thread, by the arithmetic of node_of.
 #include <cstdio>
 #include <cstring>
@@ -29,24 +30,34 @@ static bool covered(const RowGrid& g, int nx, int ny) {
     return true;
 }
 
+template <class ST>
+static VecChoice choice(const elbm_lattice* h) {
+    return h->u_mode == 0 ? choose_vec<ST, 0>(h) : h->u_mode == 1 ? choose_vec<ST, 1>(h) : choose_vec<ST, 2>(h);
+}
+
 int main() {
     char what[16], form[16];
-    int flags, u_mode, root, nx, ny, nz;
-    while (scanf("%15s %15s %d %d %d %d %d %d", what, form, &flags, &u_mode, &root, &nx, &ny, &nz) == 8) {
+    int flags, u_mode, mode, nx, ny, nz;
+    while (scanf("%15s %15s %d %d %d %d %d %d", what, form, &flags, &u_mode, &mode, &nx, &ny, &nz) == 8) {
+        const bool rows = !strcmp(what, "rows"), f64 = !strcmp(form, "f64"), f32 = !strcmp(form, "f32");
         elbm_lattice h{};
         h.cfg.nx = nx;
         h.cfg.ny = ny;
         h.cfg.nz = nz;
         h.cfg.flags = flags;
-        h.cfg.root_rho = root ? 0.0 : -1.0;
+        h.cfg.root_rho = rows && mode ? 0.0 : -1.0;
         h.n = int64_t(nx) * ny * nz;
         h.u_mode = u_mode;
+        h.t_field_mode = rows ? 0 : mode;
         h.cus = 256;
-        const RowRule rule = !strcmp(form, "f64") ? row_rule<double>(&h)
-                             : !strcmp(form, "f32") ? row_rule<float>(&h) : row_rule<_Float16>(&h);
-        const RowGrid g = grid_for(&h, rule);
-        printf("%d %d %u %u %u %u %d\n", g.rows, g.pitch, g.block.x, g.grid.x, g.grid.y, g.grid.z,
-               int(covered(g, nx, ny)));
+        if (rows) {
+            const RowGrid g = grid_for(&h, f64 ? row_rule<double>(&h) : f32 ? row_rule<float>(&h) : row_rule<_Float16>(&h));
+            printf("%d %d %u %u %u %u %d\n", g.rows, g.pitch, g.block.x, g.grid.x, g.grid.y, g.grid.z,
+                   int(covered(g, nx, ny)));
+        } else {
+            const VecChoice c = f64 ? choice<double>(&h) : f32 ? choice<float>(&h) : choice<_Float16>(&h);
+            printf("%d %d %d\n", c.V, c.W, c.waves);
+        }
     }
     return 0;
 }

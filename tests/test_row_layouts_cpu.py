@@ -1,37 +1,19 @@
 """Launch shapes of the one-node-per-thread kernels, from the library's own rule on the host: every
 node has exactly one thread at every row length, and the layout is the one that was measured to be
 faster at shapes on both sides of the rule's lines."""
-import os
-import subprocess
-
 import pytest
 
-ROOT = os.path.dirname(os.path.dirname(os.path.abspath(__file__)))
+from launch_plan import ask
+
 SR = 2 | 4  # FP32 rest and stochastic rounding
 
 
-@pytest.fixture(scope="module")
-def plan(tmp_path_factory):
-    exe = tmp_path_factory.mktemp("plan") / "launch_plan"
-    subprocess.run(["/opt/rocm/bin/hipcc", "--offload-arch=gfx950", "--offload-host-only", "-O1", "-std=c++17",
-                    "-I", os.path.join(ROOT, "include"), "-I", os.path.join(ROOT, "paper_2605_01774_amd", "csrc"),
-                    "-DELBM_Q=19", os.path.join(ROOT, "tests", "native", "launch_plan.hip"), "-o", str(exe)], check=True)
-
-    def ask(lines):
-        r = subprocess.run([str(exe)], input="\n".join(lines) + "\n", capture_output=True, text=True, check=True)
-        out = [[int(v) for v in ln.split()] for ln in r.stdout.splitlines()]
-        assert len(out) == len(lines)
-        return out
-
-    return ask
-
-
-def test_every_node_has_one_thread(plan):
+def test_every_node_has_one_thread():
     lines = [f"rows {form} {flags} {u} {root} {nx} {ny} {nz}"
              for form, flags, u, root in [("f64", 0, 2, 0), ("f32", 0, 1, 0), ("b16", SR, 0, 0), ("f32", 0, 0, 1)]
              for nx in list(range(1, 132)) + [192, 255, 256, 257, 511, 512, 513, 1025]
              for ny, nz in [(1, 1), (2, 300), (17, 16), (61, 61), (300, 600)]]
-    for line, (rows, pitch, threads, gx, gy, gz, covered) in zip(lines, plan(lines)):
+    for line, (rows, pitch, threads, gx, gy, gz, covered) in zip(lines, ask(lines)):
         nx, ny, nz = (int(v) for v in line.split()[-3:])
         assert covered == 1 and gz == nz, line
         assert threads % 64 == 0 and threads <= 512 and gx * threads >= nx, line
@@ -57,6 +39,6 @@ PACKED = [("f64", 0, 1, 32, 32, 32, 4, 32),        # 6.6 padded, 5.4 in 256 smal
 
 
 @pytest.mark.parametrize("form,flags,u,nx,ny,nz,rows,pitch", PADDED + PACKED)
-def test_layout_is_the_faster_measured_one(plan, form, flags, u, nx, ny, nz, rows, pitch):
-    got = plan([f"rows {form} {flags} {u} 0 {nx} {ny} {nz}"])[0]
+def test_layout_is_the_faster_measured_one(form, flags, u, nx, ny, nz, rows, pitch):
+    got = ask([f"rows {form} {flags} {u} 0 {nx} {ny} {nz}"])[0]
     assert got[:2] == [rows, pitch]
