@@ -27,3 +27,12 @@ def test_rows_of_many_wavefronts():
     line = ["vec b16 6 0 0 1000 64 63"]
     assert ask(line, 19)[0] == [2, 0, 8] and ask(line, 27)[0] == [0, 0, 0]
     assert ask(["vec b16 6 0 0 1000 23 22"], 19)[0] == [0, 0, 0]
+
+
+@pytest.mark.parametrize("q", [19, 27])
+def test_gpu_test_shapes_take_the_form(q):
+    import test_gpu_ragged_form as t
+    lines = [f"vec b16 {flags} 0 {mode} {nx} {ny} {nz}" for nx, ny, nz in t.SHAPES + (t.LONG if q == 19 else [])
+             for flags in (REST, SR, REST | SR) for mode in (0, 2)]
+    for line, (V, W, waves) in zip(lines, ask(lines, q)):
+        assert (V, W) == (2, 0) and waves > 0, line
