@@ -716,10 +716,13 @@ static void launch_vec_w(const elbm_lattice* h, const StepArgs<typename Store<ST
 // table; us per step, "n" is the one-node-per-thread kernel:
 //  - 16-bit forms: 4 nodes (8 bytes) per lane (decay 256^3 BF16 V1 218, V2 214, V4 210); 2 with a
 //    velocity field (256^3 V4 376, V2 333) or a tensor field at u = 0 (294 -> 272), 1 with a tensor
-//    field and a uniform velocity (256^3 BF16 V4 321, V2 296, V1 279; BF16 + rest + SR 348 -> 311);
-//  - FP32: 1, but 2 on 384-node rows, where 1 would make blocks of 6 wavefronts;
+//    field and a uniform velocity (256^3 BF16 V4 321, V2 296, V1 279; BF16 + rest + SR 348 -> 311),
+//    but there 2 where 1 would make blocks of 6 wavefronts (384 x 103 x 101 BF16 V1 73, V2 67; BF16
+//    + rest + SR V1 88, V2 73);
+//  - FP32: 1, but 2 where 1 would make blocks of 6 wavefronts;
 //  - FP64: at u = 0, 2 with a tensor (porous 384^3: V1 3750, V2 3020) and on rows of 384 and 512
-//    (844 -> 769, 932 -> 828), else 1; with a uniform velocity 1 (two nodes need 256 to 380 VGPRs,
+//    (844 -> 769, 932 -> 828) of lattices with more rows than CUs (512 x 11 x 11 V1 7.9, V2 8.2),
+//    else 1; with a uniform velocity 1 (two nodes need 256 to 380 VGPRs,
 //    one or two waves per SIMD: tensor field 128^3 V2 136, V1 112, D3Q27 185 -> 158); with a
 //    velocity field 2 (512^3: V1 12.1 ms, V2 10.1), in D3Q27 1 on rows over 256 (512 x 256 x 128:
 //    V2 2344, V1 2083).
@@ -731,35 +734,47 @@ static void launch_vec_w(const elbm_lattice* h, const StepArgs<typename Store<ST
 //    a tensor field, 7 (848, n 767); D3Q27 with a velocity field up to 256 (256^3: 2347, n 1940);
 //  - FP32 with a velocity field, 5 wavefronts (324, n 284);
 //  - plain 16-bit forms without per-node tensor and velocity, 5 to 7 (320: 154, n 129; 448: 232,
-//    n 193), in D3Q27 also with FP32 rest or stochastic rounding (323, n 254), and there with a
-//    uniform velocity on 384-node rows (BF16 488, n 378);
+//    n 193), in D3Q27 also with FP32 rest or stochastic rounding (323, n 254), and there in the plain
+//    forms with a uniform velocity at two nodes per lane in 3 (BF16 488, n 378; with FP32 rest and SR
+//    384 x 103 x 101 131, n 139);
 //  - plain 16-bit forms between walls at one node per lane (64^3: 20.3, n 8.5; 192^3: 132, n 113),
 //    the rounding forms on 64-node rows (21.6, n 10.4): their wall lanes store single 16-bit
 //    values in a branch per direction.
+// Few blocks do not share CUs, and the row-vector kernel is the faster one again: FP64 with at most
+// one block per CU, on more than half of them (320 x 15 x 12, tensor field 7.9, n 8.6; 448 x 15 x 15
+// 9.3, n 10.3; on fewer CUs n is faster, 448 x 9 x 7 6.6, n 5.6), with a tensor field at most two
+// (320 x 23 x 20 12.5, n 13.3); D3Q27 with a velocity field at most one (256 x 16 x 15 13.6, n 15.7;
+// 256 x 25 x 23 34.7, n 29.6); FP32 with a velocity field one to two in D3Q19 (320 x 23 x 20 8.9,
+// n 10.5; 320 x 15 x 12 7.6, n 6.9); D3Q27 with FP32 rest or SR at most two (448 x 19 x 18 11.1, n 11.8).
 template <class ST, int UM>
 static int preferred_width(const elbm_lattice* h) {
     const int nx = h->cfg.nx;
     const bool tensor = h->t_field_mode != 0, tnode = h->t_field_mode == 1;
-    if (sizeof(ST) == 2) return UM == 2 ? 2 : (tnode ? (UM == 1 ? 1 : 2) : 4);
-    if (sizeof(ST) == 4) return nx == 6 * 64 ? 2 : 1;
+    const bool six = nx == 6 * 64;  // one node per lane makes blocks of 6 wavefronts
+    if (sizeof(ST) == 2) return UM == 2 ? 2 : (tnode ? (UM == 1 && !six ? 1 : 2) : 4);
+    if (sizeof(ST) == 4) return six ? 2 : 1;
     if (UM == 2) return Q == 27 ? 1 : 2;
     if (UM == 1) return 1;
-    return tensor || (Q == 19 && nx > 320) ? 2 : 1;
+    return tensor || (Q == 19 && nx > 320 && (long long)h->cfg.ny * h->cfg.nz > h->cus) ? 2 : 1;
 }
 template <class ST, int UM>
 static bool prefer_one_node(const elbm_lattice* h, int V, int W) {
     const bool rs = h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING);
     const bool tnode = h->t_field_mode == 1, walls = h->cfg.bc_x == ELBM_DIRICHLET;
+    // blocks of the row-vector kernel, in CUs
+    const int rows = (W == 3 || W > 4) ? 1 : 4 / W;
+    const double load = double((h->cfg.ny + rows - 1) / rows) * h->cfg.nz / h->cus;
     if (sizeof(ST) == 8) {
-        if (UM == 2) return Q == 27 && h->cfg.nx <= 256;
-        if (UM == 1) return tnode ? W == 5 : W >= 5;
+        if (UM == 2) return Q == 27 && h->cfg.nx <= 256 && load > 1.0;
+        if (load > 0.5 && load <= 1.0) return false;
+        if (UM == 1) return tnode ? W == 5 && load > 2.0 : W >= 5;
         return W == 5 || (Q == 19 && W == 7 && !tnode);
     }
-    if (sizeof(ST) == 4) return UM == 2 && W == 5;
+    if (sizeof(ST) == 4) return UM == 2 && W == 5 && !(Q == 19 && load > 1.0 && load <= 2.0);
     if (walls && V == 1 && (!rs || W == 1)) return true;
     if (tnode || UM == 2) return false;
-    if (Q == 27 && UM == 1 && V == 2 && W == 3) return true;
-    return W >= 5 && W <= 7 && (!rs || Q == 27);
+    if (Q == 27 && UM == 1 && V == 2 && W == 3) return !rs;
+    return W >= 5 && W <= 7 && (!rs || (Q == 27 && load > 2.0));
 }
 
 // Row-vector kernel of a lattice: V nodes per lane and W wavefronts per row, nx = 64 V W with
