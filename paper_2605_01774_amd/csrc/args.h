@@ -347,6 +347,10 @@ __device__ __forceinline__ bool node_of(const Args& a, int& x, int& y) {
     } else {
         const int q = a.rows == 1 ? 0 : int((float(t) + 0.5f) * a.inv_pitch);
         x = t - q * a.pitch;
+        // keep x itself, not t, q and the pitch to make it from again: two registers, which were
+        // two too many for four wavefronts per SIMD in D3Q27's plain 16-bit forms with a velocity
+        // per node (130 VGPRs; 66 x 213 x 213 BF16 167 us per step, 143 at 128)
+        asm("" : "+v"(x));
         y = blockIdx.y * a.rows + q;
         return x < a.nx && q < a.rows && y < a.ny;
     }
