@@ -564,10 +564,9 @@ static int advance(elbm_lattice* h, const void* src, void* dst, void* lam_rec, u
     return ELBM_OK;
 }
 
-// Two time steps in one launch, as two advance() calls; *done false where the two-step kernel
-// does not take the lattice (nothing is launched then).
+// Two time steps in one launch, as two advance() calls.
 static int advance_pair(elbm_lattice* h, const void* src, void* dst, void* const (&lam)[2], uint8_t* const (&br)[2],
-                        bool* done) {
+                        const PairPlan& plan) {
     StepPair p;
     p.mult[0] = (h->pending ? 0.5 * h->pending_scale : 0.0) + 0.5 * h->src_scale;
     p.mult[1] = (h->r_mode != 0 ? 0.5 * h->src_scale : 0.0) + 0.5 * h->src_scale;
@@ -575,8 +574,7 @@ static int advance_pair(elbm_lattice* h, const void* src, void* dst, void* const
         p.lam[m] = lam[m];
         p.br[m] = br[m];
     }
-    HIP_OK(launch_step_pair(h, src, dst, p, done), "step pair");
-    if (!*done) return ELBM_OK;
+    HIP_OK(launch_step_pair(h, src, dst, p, plan), "step pair");
     h->pending = h->r_mode != 0;
     h->pending_scale = h->src_scale;
     h->time += 2;
@@ -594,22 +592,20 @@ static int do_steps(elbm_lattice* h, int64_t n_steps, void* lam_rec, uint8_t* br
     // A launch of two steps swaps the buffers once, two single steps swap them twice. An even
     // number of such launches per call leaves the state in the buffer where single steps would:
     // a captured call of an even number of steps reads on replay what it wrote before.
-    const int64_t paired = n_steps / 4 * 4;
-    bool pairs = true;
+    PairPlan plan;
+    const int64_t paired = n_steps >= 4 && plan_step_pair(h, &plan) ? n_steps / 4 * 4 : 0;
     for (int64_t s = 0; s < n_steps; ++s) {
-        if (pairs && s < paired) {
+        if (s < paired) {
             void* lam[2];
             uint8_t* br[2];
             for (int m = 0; m < 2; ++m) {
                 lam[m] = lam_rec ? static_cast<char*>(lam_rec) + (s + m) * h->n * rb : nullptr;
                 br[m] = br_rec ? br_rec + (s + m) * h->n : nullptr;
             }
-            if (int r = advance_pair(h, h->buf[h->cur], h->buf[h->cur ^ 1], lam, br, &pairs)) return r;
-            if (pairs) {
-                h->cur ^= 1;
-                s += 1;
-                continue;
-            }
+            if (int r = advance_pair(h, h->buf[h->cur], h->buf[h->cur ^ 1], lam, br, plan)) return r;
+            h->cur ^= 1;
+            s += 1;
+            continue;
         }
         void* lr = lam_rec ? static_cast<char*>(lam_rec) + s * h->n * rb : nullptr;
         uint8_t* br = br_rec ? br_rec + s * h->n : nullptr;

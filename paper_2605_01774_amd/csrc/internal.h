@@ -64,14 +64,22 @@ inline int real_bytes(int precision) { return precision == ELBM_F64 ? 8 : 4; }
 // All launchers enqueue on h->stream and return the launch status.
 hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double src_mult,
                        void* lam_rec, uint8_t* br_rec);
-// Two steps from src to dst in one launch, where the tiled kernel takes the lattice (*done
-// tells): their source multipliers and records (null: none).
+// Tiling of a launch of two steps; false if the lattice takes single steps. It depends on the
+// configuration and the coefficients set, so that one holds for a whole run.
+struct PairPlan {
+    int bx = 0, by = 0;          // columns of a tile
+    int len = 0;                 // planes of a sweep
+    int tx = 0, ty = 0, tz = 0;  // tiles in x and y, sweeps in z
+};
+bool plan_step_pair(const elbm_lattice* h, PairPlan* plan);
+// Two steps from src to dst in one launch: their source multipliers and records (null: none).
 struct StepPair {
     double mult[2];
     void* lam[2];
     uint8_t* br[2];
 };
-hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done);
+hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p,
+                            const PairPlan& plan);
 hipError_t launch_adjoint(const elbm_lattice* h, const void* state, double src_mult,
                           const void* lam_rec, const uint8_t* br_rec, const void* adj_in,
                           void* adj_out, void* t_grad);

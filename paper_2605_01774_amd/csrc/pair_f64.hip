@@ -3,8 +3,10 @@
 
 namespace elbm {
 
-hipError_t launch_step_pair_f64(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done) {
-    return step_pair<double>(h, src, dst, p, done);
+bool plan_step_pair_f64(const elbm_lattice* h, PairPlan* plan) { return plan_pair<double>(h, plan); }
+hipError_t launch_step_pair_f64(const elbm_lattice* h, const void* src, void* dst, const StepPair& p,
+                                const PairPlan& plan) {
+    return step_pair<double>(h, src, dst, p, plan);
 }
 
 }  // namespace elbm

@@ -41,10 +41,7 @@ namespace elbm {
 
 // Tiling of a two-step launch, and what its second step has of its own.
 template <class Real>
-struct PairArgs {
-    int bx, by;      // columns of a tile
-    int len;         // planes of a sweep
-    int tx, ty, tz;  // tiles in x and y, sweeps in z
+struct PairArgs : PairPlan {
     Real src_mult;   // source multiplier of the second step
     Real* lam_rec;   // its records
     uint8_t* br_rec;
@@ -299,19 +296,24 @@ constexpr int pair_threads() {
 // on each side of a row's loads, and one more for the 10 shifted runs of 19 stored. A tensor
 // field adds 6 values per node to the loads of the first step and to those of the second, a
 // material table about 0.3. Measured against it over widths of 16 to 384, 1 to 28 rows and 240
-// to 2500 tiles: within 10 %, and the tiling it picks is the fastest measured one or within 4 %
+// to 2500 tiles: within 16 %, and the tiling it picks is the fastest measured one or within 4 %
 // of it (64^3 to 384^3 and four ragged lattices). Single steps: 6.0 TB/s and 2 us of launch.
+//
 // The two-step kernel is taken when it is estimated 10 % faster: at 64^3 FP32 it is not (8.6
-// against 10.8 us), at 96^3 it is (24 against 18; measured 21.6 and 19.0).
+// against 10.8 us), at 96^3 it is (24 against 18; measured 21.6 and 19.0). In FP64 on tiles of
+// whole rows, without a tensor field, a source per node adds 10 % and walls 13 % to an iteration,
+// which the two rows of a tile at 80^3 to 128^3 do not hide: measured against single steps 0.84
+// (112^3 between walls with a source) to 1.02 of their speed at the lattices that this declines
+// beyond the estimate without it, with 1.04 to 1.12 at seven more. FP32 (1.02 and more with both)
+// and tiles with halo columns (1.04 and more) have room for them.
 template <class Real>
-static bool pair_plan(const elbm_lattice* h, PairArgs<Real>& g) {
+static bool pair_plan(const elbm_lattice* h, PairPlan& g) {
     const long long nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz, cus = h->cus;
     constexpr int NT = pair_threads<Real>(), SB = int(sizeof(Real)), line = 128 / SB;
     if (nx * ny * Q * SB >= (1LL << 31)) return false;
     const double t_runs = h->t_field_mode == 1 ? 6.0 : 0.0, p_runs = h->t_field_mode == 2 ? 0.3 : 0.0;
-    const double single = 2.0 * (double(h->n) * SB * (2 * Q + t_runs + p_runs) / 6.0e6 + 2.0);
-    double best = 0.9 * single;
-    bool found = false;
+    const double s_runs = h->r_mode == 2 ? 1.0 : 0.0;
+    double best = 0.0;
     auto consider = [&](long long w, int hx) {
         const long long rows = NT / (w + 2 * hx) - 2;
         if (rows < 1) return;
@@ -330,9 +332,8 @@ static bool pair_plan(const elbm_lattice* h, PairArgs<Real>& g) {
             tz = (nz + len - 1) / len;
             const double r = double((tx * ty * tz + cus - 1) / cus);
             const double us = r * double(len + 2) * (1.2 + 0.075 * lines);
-            if (us < best) {
+            if (best == 0.0 || us < best) {
                 best = us;
-                found = true;
                 g.bx = int(w);
                 g.by = int(by);
                 g.len = int(len);
@@ -344,19 +345,27 @@ static bool pair_plan(const elbm_lattice* h, PairArgs<Real>& g) {
     };
     consider(nx, 0);
     for (long long w = line; w < nx && w + 2 <= NT / 3; w += line) consider(w, 1);
-    return found;
+    if (best == 0.0) return false;
+    if (SB == 8 && g.tx == 1 && t_runs == 0.0)
+        best *= 1.0 + 0.1 * s_runs + (h->cfg.bc_x == ELBM_DIRICHLET ? 0.13 : 0.0);
+    const double single = 2.0 * (double(h->n) * SB * (2 * Q + t_runs + p_runs) / 6.0e6 + 2.0);
+    return best < 0.9 * single;
 }
 
-// Two steps from src to dst in one launch where pair_plan finds it faster; *done tells.
+// Whether runs of the lattice take two steps per launch, and how.
 template <class Real>
-static hipError_t step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done) {
-    *done = false;
+static bool plan_pair(const elbm_lattice* h, PairPlan* plan) {
+    // the flags that name a single-step kernel keep it
+    const int named = ELBM_FLAG_SCALAR_KERNEL | (0xF << ELBM_VECTOR_WIDTH_SHIFT);
+    return Q == 19 && h->u_mode == 0 && h->cfg.root_rho < 0 && !(h->cfg.flags & named) && pair_plan<Real>(h, *plan);
+}
+
+template <class Real>
+static hipError_t step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, const PairPlan& plan) {
     if constexpr (Q == 19) {
         constexpr int NT = pair_threads<Real>();
         PairArgs<Real> g{};
-        // the flags that name a single-step kernel keep it
-        const int named = ELBM_FLAG_SCALAR_KERNEL | (0xF << ELBM_VECTOR_WIDTH_SHIFT);
-        if (h->u_mode != 0 || h->cfg.root_rho >= 0 || (h->cfg.flags & named) || !pair_plan(h, g)) return hipSuccess;
+        static_cast<PairPlan&>(g) = plan;
         StepArgs<Real> a = make_args<Real>(h, p.mult[0]);
         a.src = src;
         a.dst = dst;
@@ -371,7 +380,6 @@ static hipError_t step_pair(const elbm_lattice* h, const void* src, void* dst, c
         else if (a.tfield) hipLaunchKernelGGL((k_step_pair<Real, true, false, NT>), grid, block, 0, h->stream, a, g);
         else if (a.abb) hipLaunchKernelGGL((k_step_pair<Real, false, true, NT>), grid, block, 0, h->stream, a, g);
         else hipLaunchKernelGGL((k_step_pair<Real, false, false, NT>), grid, block, 0, h->stream, a, g);
-        *done = true;
     }
     return hipGetLastError();
 }

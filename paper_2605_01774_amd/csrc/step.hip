@@ -14,8 +14,10 @@ ELBM_FORM_DECL(f32)
 ELBM_FORM_DECL(bf16)
 ELBM_FORM_DECL(fp16)
 #undef ELBM_FORM_DECL
-hipError_t launch_step_pair_f64(const elbm_lattice*, const void*, void*, const StepPair&, bool*);
-hipError_t launch_step_pair_f32(const elbm_lattice*, const void*, void*, const StepPair&, bool*);
+bool plan_step_pair_f64(const elbm_lattice*, PairPlan*);
+bool plan_step_pair_f32(const elbm_lattice*, PairPlan*);
+hipError_t launch_step_pair_f64(const elbm_lattice*, const void*, void*, const StepPair&, const PairPlan&);
+hipError_t launch_step_pair_f32(const elbm_lattice*, const void*, void*, const StepPair&, const PairPlan&);
 
 hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double src_mult,
                        void* lam_rec, uint8_t* br_rec) {
@@ -27,13 +29,18 @@ hipError_t launch_step(const elbm_lattice* h, const void* src, void* dst, double
     }
 }
 
-hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p, bool* done) {
-    *done = false;
+bool plan_step_pair(const elbm_lattice* h, PairPlan* plan) {
     switch (h->cfg.precision) {
-        case ELBM_F64: return launch_step_pair_f64(h, src, dst, p, done);
-        case ELBM_F32: return launch_step_pair_f32(h, src, dst, p, done);
-        default: return hipSuccess;
+        case ELBM_F64: return plan_step_pair_f64(h, plan);
+        case ELBM_F32: return plan_step_pair_f32(h, plan);
+        default: return false;
     }
+}
+
+hipError_t launch_step_pair(const elbm_lattice* h, const void* src, void* dst, const StepPair& p,
+                            const PairPlan& plan) {
+    return h->cfg.precision == ELBM_F64 ? launch_step_pair_f64(h, src, dst, p, plan)
+                                        : launch_step_pair_f32(h, src, dst, p, plan);
 }
 
 hipError_t launch_adjoint(const elbm_lattice* h, const void* state, double src_mult,

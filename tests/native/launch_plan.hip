@@ -2,12 +2,13 @@
 // prints the launch shape that the rules choose for it, without a GPU (256 compute units).
 //   rows <f64|f32|b16> <flags> <u_mode> <root> <nx> <ny> <nz>  ->  rows pitch threads grid.x grid.y grid.z covered
 //   vec <f64|f32|b16> <flags> <u_mode> <t_mode> <nx> <ny> <nz>  ->  V W waves of the row-vector kernel
+//   pair <f64|f32> <flags> <walls> <t_mode + 4 r_mode> <nx> <ny> <nz>  ->  taken bx by len tx ty tz
 // "covered" is 1 if every node of a plane has exactly one thread, by the arithmetic of node_of.
 #include <cstdio>
 #include <cstring>
 #include <vector>
 
-#include "step_kernels.h"
+#include "pair_kernel.h"
 
 using namespace elbm;
 
@@ -47,10 +48,17 @@ int main() {
         h.cfg.flags = flags;
         h.cfg.root_rho = rows && mode ? 0.0 : -1.0;
         h.n = int64_t(nx) * ny * nz;
-        h.u_mode = u_mode;
-        h.t_field_mode = rows ? 0 : mode;
+        const bool pair = !strcmp(what, "pair");
+        h.u_mode = pair ? 0 : u_mode;
+        h.cfg.bc_x = pair && u_mode ? ELBM_DIRICHLET : ELBM_PERIODIC;
+        h.t_field_mode = rows ? 0 : mode & 3;
+        h.r_mode = pair ? mode >> 2 : 0;
         h.cus = 256;
-        if (rows) {
+        if (pair) {
+            PairPlan p;
+            const bool taken = f64 ? plan_pair<double>(&h, &p) : plan_pair<float>(&h, &p);
+            printf("%d %d %d %d %d %d %d\n", int(taken), p.bx, p.by, p.len, p.tx, p.ty, p.tz);
+        } else if (rows) {
             const RowGrid g = grid_for(&h, f64 ? row_rule<double>(&h) : f32 ? row_rule<float>(&h) : row_rule<_Float16>(&h));
             printf("%d %d %u %u %u %u %d\n", g.rows, g.pitch, g.block.x, g.grid.x, g.grid.y, g.grid.z,
                    int(covered(g, nx, ny)));
