@@ -9,8 +9,9 @@ deviations, as BF16 / FP16 deviations (round to nearest even), and as BF16 / FP1
 FP32 rest population and stochastic rounding ("bf16r", "fp16r"). Every variant's error is
 taken after --err-steps steps (200) against the FP64 GPU run of the same input and step
 count, in a run of its own after the timing. A step is one launch of the step kernel over
-all 512^3 nodes (on the u = 0 sub-workloads the FP64 and FP32 forms take two steps per launch:
-their achieved_gbs counts the bytes of a launch once, half of bytes_per_lup per step). The headline runs exactly --warmup and --steps steps; the variants and
+all 512^3 nodes (on the u = 0 sub-workloads the FP64 and FP32 forms take two steps per launch, as
+each run's buffers tell: their achieved_gbs counts the populations once per launch and the
+coefficients once per step). The headline runs exactly --warmup and --steps steps; the variants and
 sub-workloads warm up and are timed for at least --min-ms (150 ms) of GPU time each, since
 kernels of a few hundred microseconds run slower for the first tens of milliseconds.
 
@@ -82,11 +83,6 @@ def counter_summary(precision: str, workload: str) -> dict:
     return vals
 
 
-def steps_per_launch(precision: str, workload: str) -> int:
-    """Steps that one launch of the step kernel takes on this workload."""
-    return int(counter_summary(precision, workload).get("steps_per_launch", 1))
-
-
 def measured_traffic(precision: str, workload: str):
     """HBM bytes per step on this workload, from the committed counter summary (FETCH_SIZE and
     WRITE_SIZE, copy-calibrated; per launch over the steps it takes), or None if the summary is
@@ -123,6 +119,29 @@ def bytes_per_lup(precision: str, prob=None, phases: bool = False) -> int:
         comps += 1 if (prob.r is not None and np.ndim(prob.r) > 0) else 0
         b += comps * rb + (1 if phases else 0)
     return b
+
+
+def moved_bytes_per_lup(precision: str, prob=None, phases: bool = False, per_launch: int = 1) -> float:
+    """Bytes that a step has to move per lattice update where a launch takes per_launch steps: the
+    populations once per launch, the coefficients in every step."""
+    populations = bytes_per_lup(precision)
+    return populations / per_launch + bytes_per_lup(precision, prob, phases) - populations
+
+
+def steps_per_launch(lat, init) -> int:
+    """Steps that a launch takes in runs of the lattice from the saved state `init` (1 or 2), from what a
+    run of four steps leaves behind: the buffer that does not hold the state holds the one before the
+    last launch. Its first 16 MB tell the state after three steps from the one after two."""
+    import torch
+    m = min(lat.pop_bytes, 1 << 24)
+    lat.load_state(*init)
+    lat.step(3)
+    three = lat.save_state()[0][:m].clone()
+    lat.load_state(*init)
+    lat.step(4)
+    state = lat.save_state()[0][:m].clone()
+    before = lat.buf_b if torch.equal(lat.buf_a[:m], state) else lat.buf_a
+    return 1 if torch.equal(before[:m], three) else 2
 
 
 def exact_phi(prob, steps):
@@ -196,9 +215,10 @@ def run_form(prob, form, steps, warmup, err_steps, phases=False, min_ms=0.0):
     del q
     mass = lat.reduce()[0]
     counters = lat.counters()
+    per_launch = steps_per_launch(lat, init)
     del lat, init
     torch.cuda.empty_cache()
-    return dict(wall_s=wall, launch_ms=launch_ms, steps=steps, warmup=n_warm, phi=phi, mass=mass,
+    return dict(wall_s=wall, launch_ms=launch_ms, per_launch=per_launch, steps=steps, warmup=n_warm, phi=phi, mass=mass,
                 k_eff=k_eff, fallback=int(counters["fallback_nodes"]),
                 nonfinite=int(counters["nonfinite"]))
 
@@ -239,10 +259,9 @@ def run_workload(wl, steps, warmup, err_steps, forms, phases, log, headline=None
         else:
             r["err"], r["mass_err"] = None, None
         del phi
-        b = bytes_per_lup(form, prob, phases)
-        per = steps_per_launch(form, wl_tag_of(wl, phases))
-        ach = b / per * prob.n / (r["launch_ms"] * 1e-3) / 1e9
-        r.update(bytes_per_lup=b, steps_per_launch=per, achieved_gbs=ach, frac=ach / HBM_PEAK_GBS,
+        per = r.pop("per_launch")
+        ach = moved_bytes_per_lup(form, prob, phases, per) * prob.n / (r["launch_ms"] * 1e-3) / 1e9
+        r.update(bytes_per_lup=bytes_per_lup(form, prob, phases), steps_per_launch=per, achieved_gbs=ach, frac=ach / HBM_PEAK_GBS,
                  mlups=prob.n * r["steps"] / r["wall_s"] / 1e6)
         out[form] = r
     del ref
