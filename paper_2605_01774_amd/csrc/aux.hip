@@ -399,9 +399,13 @@ __global__ void k_moments(StepArgs<typename Store<ST>::Real> a, int umode, doubl
 // Global sums: Neumaier-compensated accumulation per thread (grid-stride), then an FP64 sum over
 // the block, and the sum over the blocks: by the block that finishes last, in the same launch,
 // where the handle counts its blocks (synchronous calls: no two launches of a handle overlap, and
-// the handle outlives them), and by a second launch of one block otherwise, in the same order. That
-// second launch took 3.8 us after a first of 10.4 at 32^3.
+// the handle outlives them) and there are few, and by a second launch of one block otherwise, in the
+// same order. The second launch takes 3.8 us; counting, for which every block writes back its L2's
+// changes and then waits for its turn at one address, about 0.03 us a block. One launch against two
+// with the copy of the result that two used to take, us of elbm_reduce as the host sees them, FP32:
+// 128 blocks (32^3) 19.2 and 27.9, 441 25.2 and 29.2, 1024 (64^3) 38.9 and 32.7, 2048 (128^3) 94 and 84.
 constexpr int kRedThreads = 256;
+constexpr int kOneLaunchBlocks = 512;
 
 __device__ inline void neumaier(double& sum, double& comp, double v) {
     const double t = sum + v;
@@ -487,8 +491,22 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce_final(const double* part
     sum_partials(part, nb, add_mass, out, sh);
 }
 
+// Smallest of the nb block minima, by one block.
+__device__ inline void min_partials(const double* part, int nb, double* out, double* sh) {
+    double m = __builtin_huge_val();
+    for (int b = threadIdx.x; b < nb; b += kRedThreads) m = fmin(m, part[b]);
+    m = block_reduce<true>(m, sh);
+    if (threadIdx.x == 0) out[0] = m;
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_min_final(const double* part, int nb, double* out) {
+    __shared__ double sh[kRedThreads / 64];
+    min_partials(part, nb, out, sh);
+}
+
 // Smallest current population g_i (full value, as the population readout gives it, with
-// the pending source half-step) per block, grid-stride; NaN values are skipped by fmin.
+// the pending source half-step) per block, grid-stride; NaN values are skipped by fmin. ticket null:
+// the block minima only.
 template <class ST>
 __global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>::Real> a, int umode, double* part,
                                                      unsigned long long* ticket, double* out) {
@@ -511,11 +529,8 @@ __global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>
     }
     m = block_reduce<true>(m, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = m;
-    if (!last_block(ticket, &last)) return;
-    m = __builtin_huge_val();
-    for (int b = threadIdx.x; b < int(gridDim.x); b += kRedThreads) m = fmin(m, part[b]);
-    m = block_reduce<true>(m, sh);
-    if (threadIdx.x == 0) out[0] = m;
+    if (!ticket || !last_block(ticket, &last)) return;
+    min_partials(part, int(gridDim.x), out, sh);
 }
 
 // dL/dT (6 stored components) -> dL/dD or dL/dL (6 stored components), FP64.
@@ -707,6 +722,7 @@ hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3) {
 hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsigned long long* ticket) {
     const int nb = h->part_blocks;
     const double mass = double(h->n) * h->cfg.phi_ref;
+    if (nb > kOneLaunchBlocks) ticket = nullptr;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
@@ -719,12 +735,14 @@ hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsi
 
 hipError_t launch_min_population(const elbm_lattice* h, double* out) {
     const int nb = h->part_blocks;
+    unsigned long long* const ticket = nb > kOneLaunchBlocks ? nullptr : h->d_ticket;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
         hipLaunchKernelGGL(k_min<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, h->d_part,
-                           h->d_ticket, out);
+                           ticket, out);
     });
+    if (!ticket) hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kRedThreads), 0, h->stream, h->d_part, nb, out);
     return hipGetLastError();
 }
 
