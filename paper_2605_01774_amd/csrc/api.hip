@@ -330,7 +330,7 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     h->part_blocks = int(nb < kMaxPartBlocks ? nb : kMaxPartBlocks);
     if (h->part_blocks < 1) h->part_blocks = 1;
     const size_t bytes = sizeof(double) * 4 * (size_t)h->part_blocks + kCntWords * sizeof(unsigned long long) +
-                         sizeof(long long) + sizeof(unsigned long long);
+                         2 * sizeof(long long);
     void* scratch = nullptr;
     e = hipMalloc(&scratch, bytes);
     if (e != hipSuccess) {
@@ -340,9 +340,8 @@ int elbm_create(const elbm_config* cfg, elbm_lattice** out) {
     h->d_part = static_cast<double*>(scratch);
     h->d_cnt = reinterpret_cast<unsigned long long*>(h->d_part + 4 * h->part_blocks);
     h->d_flag = reinterpret_cast<long long*>(h->d_cnt + kCntWords);
-    h->d_ticket = reinterpret_cast<unsigned long long*>(h->d_flag + 1);
-    // counters, flag and ticket start at zero (4.5 us for a size that 16 bytes do not divide, 2.6 us
-    // for this one)
+    // counters and flag start at zero, with a word behind them (4.5 us for a size that 16 bytes do not
+    // divide, 2.6 us for this one)
     static_assert((kCntWords + 2) * sizeof(unsigned long long) % 16 == 0, "whole 16-byte words");
     e = hipMemset(h->d_cnt, 0, (kCntWords + 2) * sizeof(unsigned long long));
     if (e != hipSuccess) {
@@ -667,9 +666,9 @@ int elbm_reduce(elbm_lattice* h, double* out4) {
     if (!h->initialized) return fail(ELBM_ESTATE, "lattice not initialised");
     if (!h->t_set) return fail(ELBM_ESTATE, "diffusion tensor not set");
     if (int r = set_device(h)) return r;
-    // the kernel writes the sums to pinned host memory itself: no copy, one wait
+    // the last kernel writes the sums to pinned host memory itself: no copy, one wait
     if (int r = acquire_result(h)) return r;
-    HIP_OK(launch_reduce(h, h->h_out, h->d_part, h->d_ticket), "reduce");
+    HIP_OK(launch_reduce(h, h->h_out, h->d_part), "reduce");
     HIP_OK(hipStreamSynchronize(h->stream), "reduce sync");
     for (int m = 0; m < 4; ++m) out4[m] = h->h_out[m];
     return ELBM_OK;
@@ -686,7 +685,7 @@ int elbm_reduce_noalloc(elbm_lattice* h, double* out4, int64_t out4_bytes) {
     if (int r = set_device(h)) return r;
     double* part = static_cast<double*>(scratch_of(h->device));
     if (!part) return fail(ELBM_ESTATE, "static scratch not resolved on this device");
-    HIP_OK(launch_reduce(h, out4, part, nullptr), "reduce (static scratch)");
+    HIP_OK(launch_reduce(h, out4, part), "reduce (static scratch)");
     return ELBM_OK;
 }
 

@@ -397,15 +397,12 @@ __global__ void k_moments(StepArgs<typename Store<ST>::Real> a, int umode, doubl
 }
 
 // Global sums: Neumaier-compensated accumulation per thread (grid-stride), then an FP64 sum over
-// the block, and the sum over the blocks: by the block that finishes last, in the same launch,
-// where the handle counts its blocks (synchronous calls: no two launches of a handle overlap, and
-// the handle outlives them) and there are few, and by a second launch of one block otherwise, in the
-// same order. The second launch takes 3.8 us; counting, for which every block writes back its L2's
-// changes and then waits for its turn at one address, about 0.03 us a block. One launch against two
-// with the copy of the result that two used to take, us of elbm_reduce as the host sees them, FP32:
-// 128 blocks (32^3) 19.2 and 27.9, 441 25.2 and 29.2, 1024 (64^3) 38.9 and 32.7, 2048 (128^3) 94 and 84.
+// the block, and by a second launch of one block the sum over the blocks. One launch, whose last block
+// adds up, was slower wherever it was measured beyond two blocks: every block writes back its L2's
+// changes and waits for its turn at one address before it counts itself (us of elbm_reduce, FP32, two
+// launches and one: 32^3, 128 blocks, 18.1 and 19.3; 48 x 50 x 47, 441 blocks, 19.3 and 25.3;
+// 100 x 99 x 98, 2048 blocks, 36 and 74).
 constexpr int kRedThreads = 256;
-constexpr int kOneLaunchBlocks = 512;
 
 __device__ inline void neumaier(double& sum, double& comp, double v) {
     const double t = sum + v;
@@ -431,41 +428,11 @@ __device__ inline double block_reduce(double v, double* sh) {
     return v;
 }
 
-// Whether this block is the last of its launch to get here; what the others wrote before is
-// then visible to it. The ticket counts blocks over all launches and is never reset, so that it
-// stays in step whatever runs between two launches; every launch with it has gridDim.x blocks.
-__device__ inline bool last_block(unsigned long long* ticket, int* flag) {
-    if (threadIdx.x == 0) {
-        const unsigned long long t = __hip_atomic_fetch_add(ticket, 1ull, __ATOMIC_ACQ_REL, __HIP_MEMORY_SCOPE_AGENT);
-        *flag = (t + 1) % gridDim.x == 0;
-    }
-    __syncthreads();
-    return *flag != 0;
-}
-
-// Sum of the nb block partials, by one block: each thread takes a strided subset of them.
-__device__ inline void sum_partials(const double* part, int nb, double add_mass, double* out, double* sh) {
-    double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0}, r[4];
-    for (int b = threadIdx.x; b < nb; b += kRedThreads)
-#pragma unroll
-        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], part[4 * b + m]);
-#pragma unroll
-    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
-    if (threadIdx.x == 0) {
-        out[0] = add_mass + r[0];
-#pragma unroll
-        for (int m = 1; m < 4; ++m) out[m] = r[m];
-    }
-}
-
-// ticket null: the partials only
 template <class ST>
 __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<ST>::Real> a, int umode,
-                                                        double* part, unsigned long long* ticket, double add_mass,
-                                                        double* out) {
+                                                        double* part) {
     touch_args<StepArgs<typename Store<ST>::Real>>();
     __shared__ double sh[kRedThreads / 64];
-    __shared__ int last;
     double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0};
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < a.n;
          k += (long long)gridDim.x * blockDim.x) {
@@ -481,38 +448,31 @@ __global__ __launch_bounds__(kRedThreads) void k_reduce(StepArgs<typename Store<
 #pragma unroll
         for (int m = 0; m < 4; ++m) part[4 * blockIdx.x + m] = r[m];
     }
-    if (!ticket || !last_block(ticket, &last)) return;
-    sum_partials(part, int(gridDim.x), add_mass, out, sh);
 }
 
+// Sum of the nb block partials, by one block: each thread takes a strided subset of them.
 __global__ __launch_bounds__(kRedThreads) void k_reduce_final(const double* part, int nb, double add_mass,
                                                               double* out) {
     __shared__ double sh[kRedThreads / 64];
-    sum_partials(part, nb, add_mass, out, sh);
-}
-
-// Smallest of the nb block minima, by one block.
-__device__ inline void min_partials(const double* part, int nb, double* out, double* sh) {
-    double m = __builtin_huge_val();
-    for (int b = threadIdx.x; b < nb; b += kRedThreads) m = fmin(m, part[b]);
-    m = block_reduce<true>(m, sh);
-    if (threadIdx.x == 0) out[0] = m;
-}
-
-__global__ __launch_bounds__(kRedThreads) void k_min_final(const double* part, int nb, double* out) {
-    __shared__ double sh[kRedThreads / 64];
-    min_partials(part, nb, out, sh);
+    double sum[4] = {0, 0, 0, 0}, comp[4] = {0, 0, 0, 0}, r[4];
+    for (int b = threadIdx.x; b < nb; b += kRedThreads)
+#pragma unroll
+        for (int m = 0; m < 4; ++m) neumaier(sum[m], comp[m], part[4 * b + m]);
+#pragma unroll
+    for (int m = 0; m < 4; ++m) r[m] = block_reduce<false>(sum[m] + comp[m], sh);
+    if (threadIdx.x == 0) {
+        out[0] = add_mass + r[0];
+#pragma unroll
+        for (int m = 1; m < 4; ++m) out[m] = r[m];
+    }
 }
 
 // Smallest current population g_i (full value, as the population readout gives it, with
-// the pending source half-step) per block, grid-stride; NaN values are skipped by fmin. ticket null:
-// the block minima only.
+// the pending source half-step) per block, grid-stride; NaN values are skipped by fmin.
 template <class ST>
-__global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>::Real> a, int umode, double* part,
-                                                     unsigned long long* ticket, double* out) {
+__global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>::Real> a, int umode, double* part) {
     touch_args<StepArgs<typename Store<ST>::Real>>();
     __shared__ double sh[kRedThreads / 64];
-    __shared__ int last;
     double m = __builtin_huge_val();
     const ST* buf = static_cast<const ST*>(a.src);
     for (long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x; k < a.n;
@@ -529,8 +489,14 @@ __global__ __launch_bounds__(kRedThreads) void k_min(StepArgs<typename Store<ST>
     }
     m = block_reduce<true>(m, sh);
     if (threadIdx.x == 0) part[blockIdx.x] = m;
-    if (!ticket || !last_block(ticket, &last)) return;
-    min_partials(part, int(gridDim.x), out, sh);
+}
+
+__global__ __launch_bounds__(kRedThreads) void k_min_final(const double* part, int nb, double* out) {
+    __shared__ double sh[kRedThreads / 64];
+    double m = __builtin_huge_val();
+    for (int b = threadIdx.x; b < nb; b += kRedThreads) m = fmin(m, part[b]);
+    m = block_reduce<true>(m, sh);
+    if (threadIdx.x == 0) out[0] = m;
 }
 
 // dL/dT (6 stored components) -> dL/dD or dL/dL (6 stored components), FP64.
@@ -719,30 +685,26 @@ hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3) {
     return hipGetLastError();
 }
 
-hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsigned long long* ticket) {
+hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part) {
     const int nb = h->part_blocks;
-    const double mass = double(h->n) * h->cfg.phi_ref;
-    if (nb > kOneLaunchBlocks) ticket = nullptr;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
-        hipLaunchKernelGGL(k_reduce<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, part,
-                           ticket, mass, out4);
+        hipLaunchKernelGGL(k_reduce<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, part);
     });
-    if (!ticket) hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedThreads), 0, h->stream, part, nb, mass, out4);
+    hipLaunchKernelGGL(k_reduce_final, dim3(1), dim3(kRedThreads), 0, h->stream, part, nb,
+                       double(h->n) * h->cfg.phi_ref, out4);
     return hipGetLastError();
 }
 
 hipError_t launch_min_population(const elbm_lattice* h, double* out) {
     const int nb = h->part_blocks;
-    unsigned long long* const ticket = nb > kOneLaunchBlocks ? nullptr : h->d_ticket;
     ELBM_DISPATCH(h, {
         auto a = make_args<typename Store<ST>::Real>(h, h->pending ? h->pending_scale : 0.0);
         a.src = h->buf[h->cur];
-        hipLaunchKernelGGL(k_min<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, h->d_part,
-                           ticket, out);
+        hipLaunchKernelGGL(k_min<ST>, dim3(nb), dim3(kRedThreads), 0, h->stream, a, h->u_mode, h->d_part);
     });
-    if (!ticket) hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kRedThreads), 0, h->stream, h->d_part, nb, out);
+    hipLaunchKernelGGL(k_min_final, dim3(1), dim3(kRedThreads), 0, h->stream, h->d_part, nb, out);
     return hipGetLastError();
 }
 

@@ -45,7 +45,6 @@ struct elbm_lattice {
     double* d_part = nullptr;             // reduction partials
     unsigned long long* d_cnt = nullptr;  // step counters, spread over slots (lattice.h)
     long long* d_flag = nullptr;          // first bad node (validation)
-    unsigned long long* d_ticket = nullptr;  // blocks that finished a synchronous reduction, never reset
     double* h_out = nullptr;              // pinned host memory that synchronous reductions write to
     int h_slot = -1;                      // its slot, -1: the handle's own allocation
     int part_blocks = 0;
@@ -92,9 +91,8 @@ hipError_t launch_get_pops(const elbm_lattice* h, double* f);
 hipError_t launch_set_pops(const elbm_lattice* h, const double* f, void* dst);
 hipError_t launch_moments(const elbm_lattice* h, double* phi, double* q3);
 // part: 4 * h->part_blocks doubles of device scratch for the block partials; the result goes to
-// device memory or to the handle's pinned host memory. ticket null: no memory of the handle is
-// used (two launches)
-hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part, unsigned long long* ticket);
+// device memory or to the handle's pinned host memory
+hipError_t launch_reduce(const elbm_lattice* h, double* out4, double* part);
 hipError_t launch_min_population(const elbm_lattice* h, double* out);
 hipError_t launch_stream_copy(const elbm_lattice* h, const void* src, void* dst, size_t words16);
 // T of `count` tensors (count = n for a field, nphase for a material table)
