@@ -232,17 +232,16 @@ __device__ inline void put_node(const StepArgs<typename Store<ST>::Real>& a, ST*
 template <class ST, int MODE>
 __global__ void k_init(StepArgs<typename Store<ST>::Real> a, int umode, const double* phi0,
                        const double* j0) {
-    touch_args<StepArgs<typename Store<ST>::Real>>();
     const long long k = (long long)blockIdx.x * blockDim.x + threadIdx.x;
     if (k >= a.n) return;
-    const double p = phi0[k];
     double g[Q];
     if constexpr (MODE == 0) {
 #pragma unroll
-        for (int i = 0; i < Q; ++i) g[i] = weight(i) * (p - double(a.phi_ref));
+        for (int i = 0; i < Q; ++i) g[i] = weight(i) * (phi0[k] - double(a.phi_ref));
     } else {
         double u[3];
         node_u64(a, umode, k, u);
+        const double p = phi0[k];
         const double jx = j0 ? j0[k] : 0.0, jy = j0 ? j0[a.n + k] : 0.0, jz = j0 ? j0[2 * a.n + k] : 0.0;
 #pragma unroll
         for (int i = 0; i < Q; ++i)
