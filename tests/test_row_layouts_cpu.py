@@ -42,3 +42,12 @@ PACKED = [("f64", 0, 1, 32, 32, 32, 4, 32),        # 6.6 padded, 5.4 in 256 smal
 def test_layout_is_the_faster_measured_one(form, flags, u, nx, ny, nz, rows, pitch):
     got = ask([f"rows {form} {flags} {u} 0 {nx} {ny} {nz}"])[0]
     assert got[:2] == [rows, pitch]
+
+
+def test_gpu_test_lattices_take_their_layouts():
+    import test_gpu_row_layouts as t
+    for prec, opts, velocity, nx, ny, nz, parts, rows, pitch in t.CASES:
+        form = prec if prec in ("f64", "f32") else "b16"
+        head = f"rows {form} {2 if opts else 0} {2 if velocity == 'field' else 1} 0 {nx} {ny}"
+        whole, part = ask([f"{head} {nz}", f"{head} {nz // parts}"])
+        assert whole[:2] == [rows, pitch] and part[:2] != whole[:2], head
