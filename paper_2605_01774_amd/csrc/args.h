@@ -320,7 +320,7 @@ inline RowGrid grid_for(const elbm_lattice* h, const RowRule& rule, int max_thre
             const bool halved = nx > 16 && nx < 32;  // padded to two rows per wavefront
             if (fewer && even && (waves(most * nx) == 4 || many) && !rule.paced && (!halved || (rule.arith && nx <= 21)))
                 packed = most;
-            else if (many && nx > 64)
+            else if (many && nx > 64 && ny <= 65535)  // one row per block in y, as far as a grid goes
                 packed = 1;  // alone, its row in scalar registers (step_t): 1.03-1.08 times padded pairs
         }
         if (packed) {

@@ -51,3 +51,12 @@ def test_gpu_test_lattices_take_their_layouts():
         head = f"rows {form} {2 if opts else 0} {2 if velocity == 'field' else 1} 0 {nx} {ny}"
         whole, part = ask([f"{head} {nz}", f"{head} {nz // parts}"])
         assert whole[:2] == [rows, pitch] and part[:2] != whole[:2], head
+
+
+@pytest.mark.parametrize("form,flags", [("f64", 0), ("f32", 0), ("b16", 0), ("b16", SR)])
+def test_long_planes_stay_within_a_grid(form, flags):
+    """Rows up to 128 nodes in a plane of 131 070 rows (65 535 blocks of two), which padded rows
+    reach: no layout has more blocks in y than a grid takes."""
+    lines = [f"rows {form} {flags} 1 0 {nx} 131070 1" for nx in (1, 16, 17, 32, 33, 64, 65, 85, 90, 97, 110, 128)]
+    for line, (rows, pitch, threads, gx, gy, gz, covered) in zip(lines, ask(lines)):
+        assert gy <= 65535 and covered == 1, line
