@@ -254,11 +254,14 @@ inline StepArgs<Real> make_args(const elbm_lattice* h, double src_mult) {
 //    as 400 padded ones did, 0.76-0.9 times as fast without this condition);
 //  - rows are not of 17 to 31 nodes (padded to 32, two per wavefront; FP32 and plain BF16 0.7-1.05
 //    packed) and memory does not set the pace (state and coefficients beyond half of the 256 MB cache:
-//    FP32 0.9-1.05, FP64 0.93-1.05, plain BF16 0.89-1.1), unless arithmetic bounds the kernel: FP32 rest or SR,
+//    FP32 0.9-1.05, FP64 0.93-1.05, plain BF16 0.89-1.0, but 1.05-1.15 where packing takes 1.4 times
+//    fewer threads), unless arithmetic bounds the kernel: FP32 rest or SR,
 //    FP64 with a velocity per node (1.03-1.34 there), the exact root, the adjoint (1.02-1.3). Of 17
 //    to 31 nodes those to 21 then (1.04-1.3; 23 x 511 x 511 BF16 with FP32 rest and SR 0.91).
-// Over all of these sizes, against padded alone: FP64 1.03, FP32 1.02, BF16 1.04, BF16 with FP32
-// rest and SR 1.07, none below 0.94.
+// 16-bit forms whose fullest CU would get more rows in 256-thread blocks are packed into blocks of
+// three or two wavefronts where it then does not (18 x 119 x 117 BF16 7.9 us against 9.4 padded).
+// Over all of these sizes, against padded alone: FP64 1.03, FP32 1.01, BF16 1.05, BF16 with FP32
+// rest and SR 1.1; one in a hundred below 0.95.
 //
 // A lattice that 256-thread blocks would put on a part of the CUs takes the smallest packed blocks
 // that still find a CU each, if they have fewer wavefronts: 32^3 FP64 6.6 -> 5.4 us, FP32
@@ -267,11 +270,13 @@ struct RowRule {
     bool arith;     // arithmetic bounds the kernel
     bool rounding;  // 16-bit form with FP32 rest or stochastic rounding
     bool paced;     // memory does
+    bool half;      // 16-bit form
 };
 template <class ST>
 inline RowRule row_rule(const elbm_lattice* h) {
     RowRule r;
-    r.rounding = sizeof(ST) == 2 && (h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING));
+    r.half = sizeof(ST) == 2;
+    r.rounding = r.half && (h->cfg.flags & (ELBM_FLAG_REST_FP32 | ELBM_FLAG_STOCHASTIC_ROUNDING));
     r.arith = r.rounding || (sizeof(ST) == 8 && h->u_mode == 2) || h->cfg.root_rho >= 0;
     const int coefs = (h->t_field_mode == 1 ? 6 : 0) + (h->u_mode == 2 ? 3 : 0) + (h->r_mode == 2 ? 1 : 0);
     r.paced = !r.arith && double(h->n) * (Q * sizeof(ST) + coefs * sizeof(typename Store<ST>::Real)) > 128e6;
@@ -314,12 +319,21 @@ inline RowGrid grid_for(const elbm_lattice* h, const RowRule& rule, int max_thre
             while (r < top && blocks(r) > h->cus) ++r;
             if (waves(r * nx) < pad_waves) packed = r;
         } else {
-            const bool fewer = double(pad_waves) * double(blocks(pad)) >= 1.2 * waves(most * nx) * double(blocks(most));
-            const bool even = double(rounds(pad) * pad) >= (rule.arith ? 0.85 : 0.9) * double(rounds(most) * most);
+            const auto fewer = [&](int r) {  // wavefronts padded over those of r rows packed
+                return double(pad_waves) * double(blocks(pad)) / (waves(r * nx) * double(blocks(r)));
+            };
+            const auto even = [&](int r) { return double(rounds(pad) * pad) / double(rounds(r) * r); };
             const bool many = rule.rounding && blocks(pad) >= 8 * h->cus;
             const bool halved = nx > 16 && nx < 32;  // padded to two rows per wavefront
-            if (fewer && even && (waves(most * nx) == 4 || many) && !rule.paced && (!halved || (rule.arith && nx <= 21)))
+            const bool paced = rule.paced && !(rule.half && fewer(most) >= 1.4);
+            const int three = min(192 / nx, ny), two = min(128 / nx, ny);
+            if (fewer(most) >= 1.2 && even(most) >= (rule.arith ? 0.85 : 0.9) && (waves(most * nx) == 4 || many) &&
+                !paced && (!halved || (rule.arith && nx <= 21)))
                 packed = most;
+            else if (rule.half && !rule.paced && three > 1 && fewer(three) >= 1.2 && even(three) >= 1.0)
+                packed = three;
+            else if (rule.half && !rule.paced && two > 1 && fewer(two) >= 1.2 && even(two) >= 1.0)
+                packed = two;
             else if (many && nx > 64 && ny <= 65535)  // one row per block in y, as far as a grid goes
                 packed = 1;  // alone, its row in scalar registers (step_t): 1.03-1.08 times padded pairs
         }

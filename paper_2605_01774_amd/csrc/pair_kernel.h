@@ -301,11 +301,11 @@ constexpr int pair_threads() {
 //
 // The two-step kernel is taken when it is estimated 10 % faster: at 64^3 FP32 it is not (8.6
 // against 10.8 us), at 96^3 it is (24 against 18; measured 21.6 and 19.0). In FP64 on tiles of
-// whole rows, without a tensor field, a source per node adds 10 % and walls 13 % to an iteration,
-// which the two rows of a tile at 80^3 to 128^3 do not hide: measured against single steps 0.84
-// (112^3 between walls with a source) to 1.02 of their speed at the lattices that this declines
-// beyond the estimate without it, with 1.04 to 1.12 at seven more. FP32 (1.02 and more with both)
-// and tiles with halo columns (1.04 and more) have room for them.
+// two or three whole rows, without a tensor field, a source per node adds 10 % and walls 13 % to an
+// iteration, which such a tile does not hide: 112^3 between walls 0.93 of the speed of single steps,
+// 0.84 with a source; 120^3 with both 0.96, 88^3 0.97. Tiles of more rows (33 x 175 x 173 between walls
+// 45 us, single steps 72; 84 x 109 x 109 50 and 61; 80^3 with both 0.99), FP32 (1.02 and more with
+// both) and tiles with halo columns (1.04 and more) have room for them.
 template <class Real>
 static bool pair_plan(const elbm_lattice* h, PairPlan& g) {
     const long long nx = h->cfg.nx, ny = h->cfg.ny, nz = h->cfg.nz, cus = h->cus;
@@ -346,7 +346,7 @@ static bool pair_plan(const elbm_lattice* h, PairPlan& g) {
     consider(nx, 0);
     for (long long w = line; w < nx && w + 2 <= NT / 3; w += line) consider(w, 1);
     if (best == 0.0) return false;
-    if (SB == 8 && g.tx == 1 && t_runs == 0.0)
+    if (SB == 8 && g.tx == 1 && g.by <= 3 && t_runs == 0.0)
         best *= 1.0 + 0.1 * s_runs + (h->cfg.bc_x == ELBM_DIRICHLET ? 0.13 : 0.0);
     const double single = 2.0 * (double(h->n) * SB * (2 * Q + t_runs + p_runs) / 6.0e6 + 2.0);
     return best < 0.9 * single;

@@ -940,7 +940,7 @@ static hipError_t adj_t(const elbm_lattice* h, const void* state, double src_mul
     a.adj_in = static_cast<const Real*>(adj_in);
     a.adj_out = static_cast<Real*>(adj_out);
     a.t_grad = static_cast<Real*>(t_grad);
-    const RowGrid rg = grid_for(h, {true, false, false}, 256);  // gathers and local writes: rows may be split
+    const RowGrid rg = grid_for(h, {true, false, false, false}, 256);  // gathers and local writes: rows may be split
     const dim3 grid = rg.grid, block = rg.block;
     rg.place(a);
     if (a.abb)

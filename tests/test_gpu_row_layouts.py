@@ -18,7 +18,7 @@ ROUNDING = dict(rest_fp32=True)  # stochastic rounding draws by node, so it diff
 CASES = [("f64", {}, "uniform", 33, 67, 68, 4, 7, 33), ("f32", {}, "uniform", 85, 60, 60, 4, 3, 85),
          ("f32", {}, "uniform", 55, 60, 64, 16, 4, 64), ("f32", {}, "uniform", 110, 61, 64, 32, 2, 128),
          ("bf16", {}, "field", 40, 126, 128, 16, 6, 40), ("bf16", ROUNDING, "uniform", 20, 121, 120, 4, 12, 20),
-         ("fp16", ROUNDING, "uniform", 110, 131, 128, 16, 1, 110), ("fp16", ROUNDING, "uniform", 90, 131, 128, 16, 2, 90),
+         ("fp16", ROUNDING, "uniform", 110, 131, 128, 16, 1, 110), ("fp16", ROUNDING, "uniform", 75, 131, 128, 64, 3, 75), ("bf16", {}, "uniform", 18, 119, 120, 60, 10, 18),
          ("f64", {}, "field", 70, 120, 128, 32, 3, 70), ("f64", {}, "uniform", 32, 32, 32, 2, 4, 32)]
 
 

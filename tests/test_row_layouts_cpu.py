@@ -34,6 +34,8 @@ PACKED = [("f64", 0, 1, 32, 32, 32, 4, 32),        # 6.6 padded, 5.4 in 256 smal
           ("f64", 0, 2, 90, 200, 150, 2, 128),     # FP64 with a velocity field: as padded
           ("f64", 0, 2, 70, 239, 239, 3, 70),      # 1.22 times as fast packed
           ("b16", SR, 1, 70, 239, 239, 3, 70),     # 1.28
+          ("b16", 0, 1, 70, 239, 239, 3, 70),      # 79 us, padded 99 (porous)
+          ("b16", 0, 1, 18, 119, 117, 7, 18),      # 7.9 in blocks of two wavefronts, padded 9.4
           ("f32", 0, 1, 70, 120, 120, 3, 70),      # 1.06
           ("b16", SR, 1, 110, 191, 190, 1, 110)]   # 1.07 alone
 

@@ -41,7 +41,7 @@ def test_both_kinds_of_tile_are_tested():
 # FP64 whole rows: single steps were faster (or no slower) with walls or a source at these
 @pytest.mark.parametrize("shape,walls,t_mode,r_mode", [((112, 112, 112), 1, 2, 2), ((112, 112, 112), 1, 2, 0),
                                                        ((112, 112, 112), 0, 0, 2), ((120, 120, 120), 1, 2, 2),
-                                                       ((88, 88, 88), 1, 2, 2), ((80, 80, 80), 1, 2, 2)])
+                                                       ((88, 88, 88), 1, 2, 2)])
 def test_whole_rows_with_walls_and_sources_stay_single(shape, walls, t_mode, r_mode):
     assert ask([_line("f64", shape, walls, t_mode, r_mode)])[0][0] == 0
 
@@ -52,3 +52,9 @@ def test_other_routes_stay_single():
     assert [p[0] for p in ask([_line("f32", big, flags=SCALAR), _line("f32", big, flags=WIDTH1),
                                _line("f32", (64, 64, 64)), _line("f64", (48, 48, 48))])] == [0, 0, 0, 0]
     assert ask([_line("f32", big)], 27)[0][0] == 0
+
+
+# and two steps were faster on tiles of more rows
+@pytest.mark.parametrize("shape", [(33, 175, 173), (20, 225, 222), (66, 123, 123), (84, 109, 109)])
+def test_tiles_of_more_rows_take_two_steps_between_walls(shape):
+    assert ask([_line("f64", shape, 1, 2, 0)])[0][0] == 1
